@@ -365,18 +365,11 @@ cpm_status cpm_batch_solve(cpm_batch* batch, const cpm_solve_opts* opts,
 /* Autotuner: time every launch variant of cpm_apply for this band, dtype and
  * nrhs with HIP events, `reps` calls each, and keep the fastest for later
  * calls with this dtype.  Variant k = 8 lap + 2 mode + pad (0 <= k < 32):
- * pad is the LDS line padding of the staged cube (0: 1 element, 1: 4
- * elements); mode 0 visits tiles and blocks in block order, mode 1 gives each
- * XCD a contiguous range of them, mode 2 runs the tile gather as persistent
- * wavefronts over such ranges that request the next tile's metadata early,
- * mode 3 also its staged values (modes 2 and 3 are for bands only: a batch's
- * composite skips them and reports HUGE_VAL); lap 0 gathers every FD
- * neighbour of the Laplacian pass from memory, lap 1 exchanges in-block
- * neighbours between lanes, lap 2 does the same in persistent wavefronts
- * that request the next block's data while finishing the current one (one
- * right-hand side; with several the pass runs as lap 1), lap 3 takes two
- * blocks per wavefront with their metadata in scalar registers and exchanges
- * in-block neighbours with row moves and lane permutes.  u and v are
+ * pad is the LDS line padding of the staged cube in elements; mode 0 visits
+ * supertiles and blocks in block order, modes 1 to 3 give each XCD a
+ * contiguous range of them (for a batch's composite modes 2 and 3 are skipped
+ * and reported as HUGE_VAL); lap selects nothing: the Laplacian pass has one
+ * form.  Variants that launch the same kernels are timed once.  u and v are
  * scratch device arrays [nrhs][n] of that dtype.  ms (may be NULL) receives
  * the 32 mean times per call; *best (may be NULL) the chosen variant.
  * Synchronises the stream. */

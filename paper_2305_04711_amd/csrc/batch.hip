@@ -31,15 +31,22 @@ constexpr int kChunk = 32768;  // elements per reduction workgroup (256 x 128)
 constexpr int kBT = 256;
 
 // ---------------------------------------------------------------- concat
-__global__ void k_cat_meta(const QMeta* in, QMeta* out, int64_t cnt, int add, int face_inst) {
+__global__ void k_cat_meta(const QMeta* in, QMeta* out, int64_t cnt, int add) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= cnt) return;
   QMeta q = in[i];
-  if (face_inst >= 0 && (i & 7) == 7) {
-    q.pad = face_inst;   // block metadata: instance id in entry 7
-  } else {
-    q.off += add;
-  }
+  q.off += add;
+  out[i] = q;
+}
+
+// block metadata, with the instance id in every block's entry 7; blocks past
+// the instance's own (padding) are empty
+__global__ void k_cat_face(const QMeta* in, QMeta* out, int nb, int nb_pad, int add, int inst) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (int64_t)nb_pad * 8) return;
+  QMeta q = i < (int64_t)nb * 8 ? in[i] : QMeta{0ull, 0, -1};
+  if ((i & 7) == 7) q.pad = inst;
+  else q.off += add;
   out[i] = q;
 }
 
@@ -48,6 +55,14 @@ __global__ void k_cat_int(const int* in, int* out, int64_t cnt, int add) {
   if (i >= cnt) return;
   const int v = in[i];
   out[i] = v >= 0 ? v + add : v;
+}
+
+// supertile ranges: slots shifted by add, the instance filled in
+__global__ void k_cat_rng(const int4* in, int4* out, int64_t cnt, int add, int inst) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= cnt) return;
+  const int4 r = in[i];
+  out[i] = make_int4(r.x + add, r.y, inst, 0);
 }
 
 __global__ void k_fill_int(int* out, int64_t cnt, int val) {
@@ -150,9 +165,9 @@ __global__ __launch_bounds__(256) void k_bs(int nchunks, Seg g, const T* __restr
 
 // Finishes a dot product fused into the composite apply, one workgroup per
 // system s = r * ninst + i: the partials of right-hand side r lie at dp + 2 r
-// np (first value) and + np (second value); instance i owns the Laplacian
-// pass's block partials [boff[i], boff[i + 1]) and the explicit rows'
-// partials lp0 + [loff[i], loff[i + 1]).  Summed in a fixed order.  MODE 0:
+// np (first value) and + np (second value), one partial per workgroup of the
+// Laplacian pass; instance i owns the explicit rows' [loff[i], loff[i + 1])
+// and the blocks' lp0 + [boff[i], boff[i + 1]).  Summed in a fixed order.  MODE 0:
 // alpha = rho / (rh, v); MODE 1: omega = (t, s) / (t, t).
 template <int MODE>
 __global__ __launch_bounds__(256) void k_bdot_fin(int ninst, const double* __restrict__ dp,
@@ -163,11 +178,11 @@ __global__ __launch_bounds__(256) void k_bdot_fin(int ninst, const double* __res
   if (S[s].done) return;
   const double* d = dp + (size_t)2 * r * np;
   double v[2] = {0.0, 0.0};
-  for (int k = boff[i] + threadIdx.x; k < boff[i + 1]; k += kBT) {
+  for (int k = lp0 + boff[i] + threadIdx.x; k < lp0 + boff[i + 1]; k += kBT) {
     v[0] += d[k];
     v[1] += d[np + k];
   }
-  for (int k = lp0 + loff[i] + threadIdx.x; k < lp0 + loff[i + 1]; k += kBT) {
+  for (int k = loff[i] + threadIdx.x; k < loff[i + 1]; k += kBT) {
     v[0] += d[k];
     v[1] += d[np + k];
   }
@@ -306,9 +321,9 @@ struct cpm_batch {
   int* sfirst = nullptr;
   int* snch = nullptr;
   std::vector<int> h_csys;
-  // per instance, the range of the composite's blocks and of its explicit FD
-  // rows ([ninst + 1] each): the partials of a dot product fused into the
-  // composite apply that belong to the instance
+  // per instance, the workgroups of the Laplacian pass that hold its blocks
+  // and its explicit FD rows ([ninst + 1] each): the partials of a dot product
+  // fused into the composite apply that belong to the instance
   std::vector<int> h_boff, h_loff;
   int* boff = nullptr;
   int* loff = nullptr;
@@ -343,78 +358,81 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   c->N = b0->N;
   c->p = b0->p;
   c->composite = true;
-  int64_t nb = 0, nt = 0, ntr = 0, ne = 0, nl = 0;
+  // blocks and explicit FD rows of an instance are padded to whole workgroups
+  // of the Laplacian pass, so that a workgroup's dot partial has one owner
+  constexpr int kBlkPad = 8, kRowPad = 256;
+  auto up = [](int64_t n, int to) { return (n + to - 1) / to * to; };
+  int64_t nb = 0, nt = 0, ns = 0, ne = 0, nl = 0;
   B->D.assign(ni + 1, 0);
   for (int i = 0; i < ni; ++i) {
     const cpm_band* b = B->bands[i];
     if (b->dim != c->dim) CPM_FAIL(CPM_E_INVALID, "a batch needs bands of one dimension");
     if (b->p != c->p) CPM_FAIL(CPM_E_INVALID, "a batch needs bands of one interpolation degree");
     B->D[i + 1] = B->D[i] + b->n;
-    nb += b->nb;
-    nt += b->ntiles;
-    ntr += b->n_tile_rows;
+    nb += up(b->nb, kBlkPad);
+    nt += b->nst;
+    ns += b->n_slots;
     ne += b->n_erows;
-    nl += b->n_lrows;
+    nl += up(b->n_lrows, kRowPad);
   }
   B->total = B->D[ni];
   if (B->total * B->nrhs >= (1ll << 31)) CPM_FAIL(CPM_E_INVALID, "batch too large");
-  const int d = c->dim, nm = d == 3 ? 64 : 16, nf = 2 * d;
+  const int d = c->dim, nm = d == 3 ? 64 : 16, nf = 2 * d, nq = d == 3 ? 18 : 9;
   c->n = c->n_s = B->total;
   c->nb = (int)nb;
-  c->ntiles = (int)nt;
-  c->n_tile_rows = (int)ntr;
+  c->nst = (int)nt;
+  c->n_slots = ns;
   c->n_erows = (int)ne;
   c->n_lrows = (int)nl;
   c->blk_face = c->alloc<QMeta>((size_t)nb * 8);
-  c->tile_meta = c->alloc<QMeta>((size_t)nt * 8);
-  c->tile_start = c->alloc<int>(nt + 1);
-  c->perm = c->alloc<int>(ntr);
-  c->frac64 = c->alloc<double>((size_t)d * ntr);
-  c->frac32 = c->alloc<float>((size_t)d * ntr);
-  c->lbase = c->alloc<unsigned>(ntr);
+  c->st_meta = c->alloc<QMeta>((size_t)nt * nq);
+  c->st_rng = c->alloc<int4>(nt);
+  c->slot_dof = c->alloc<int2>(ns);
+  c->slot_base = c->alloc<unsigned short>(ns);
+  c->slot_frac64 = c->alloc<double2>((size_t)d * ns);
+  c->slot_frac32 = c->alloc<float2>((size_t)d * ns);
   c->erow_id = c->alloc<int>(ne);
   c->ecol = c->alloc<int>((size_t)ne * nm);
   c->ew = c->alloc<double>((size_t)ne * nm);
-  c->ew32 = c->alloc<float>((size_t)ne * nm);
   c->lrow_id = c->alloc<int>(nl);
   c->lcol = c->alloc<int>((size_t)nl * nf);
   c->lrow_inst = c->alloc<int>(nl);
   c->erow_inst = c->alloc<int>(ne);
-  c->tile_inst = c->alloc<int>(nt);
   c->inst_skip = c->alloc<int>((size_t)ni * B->nrhs);
   c->skip_stride = ni;
   CPM_HIP(hipMemsetAsync(c->inst_skip, 0, sizeof(int) * ni * B->nrhs, st));
+  CPM_HIP(hipMemsetAsync(c->lrow_id, 0xff, sizeof(int) * nl, st));
   c->inst_coef = c->alloc<double>((size_t)2 * ni);
-  int64_t ob = 0, ot = 0, otr = 0, oe = 0, ol = 0;
+  int64_t ob = 0, ot = 0, os = 0, oe = 0, ol = 0;
   B->h_boff.assign(ni + 1, 0);
   B->h_loff.assign(ni + 1, 0);
   auto g = [](int64_t n) { return dim3(grid_for(n, 256)); };
   for (int i = 0; i < ni; ++i) {
     const cpm_band* b = B->bands[i];
     const int add = (int)B->D[i];
-    hipLaunchKernelGGL(k_cat_meta, g((int64_t)b->nb * 8), dim3(256), 0, st, b->blk_face,
-                       c->blk_face + ob * 8, (int64_t)b->nb * 8, add, i);
-    hipLaunchKernelGGL(k_cat_meta, g((int64_t)b->ntiles * 8), dim3(256), 0, st, b->tile_meta,
-                       c->tile_meta + ot * 8, (int64_t)b->ntiles * 8, add, -1);
-    hipLaunchKernelGGL(k_cat_int, g(b->ntiles), dim3(256), 0, st, b->tile_start,
-                       c->tile_start + ot, (int64_t)b->ntiles, (int)otr);
-    hipLaunchKernelGGL(k_cat_int, g(b->n_tile_rows), dim3(256), 0, st, b->perm, c->perm + otr,
-                       (int64_t)b->n_tile_rows, add);
+    const int nbp = (int)up(b->nb, kBlkPad);
+    hipLaunchKernelGGL(k_cat_face, g((int64_t)nbp * 8), dim3(256), 0, st, b->blk_face,
+                       c->blk_face + ob * 8, b->nb, nbp, add, i);
+    hipLaunchKernelGGL(k_cat_meta, g((int64_t)b->nst * nq), dim3(256), 0, st, b->st_meta,
+                       c->st_meta + ot * nq, (int64_t)b->nst * nq, add);
+    hipLaunchKernelGGL(k_cat_rng, g(b->nst), dim3(256), 0, st, b->st_rng, c->st_rng + ot,
+                       (int64_t)b->nst, (int)os, i);
+    hipLaunchKernelGGL(k_cat_int, g(2 * b->n_slots), dim3(256), 0, st,
+                       reinterpret_cast<const int*>(b->slot_dof),
+                       reinterpret_cast<int*>(c->slot_dof + os), 2 * b->n_slots, add);
     for (int a = 0; a < d; ++a) {
-      CPM_HIP(hipMemcpyAsync(c->frac64 + (int64_t)a * ntr + otr, b->frac64 + (int64_t)a * b->n_tile_rows,
-                             sizeof(double) * b->n_tile_rows, hipMemcpyDeviceToDevice, st));
-      CPM_HIP(hipMemcpyAsync(c->frac32 + (int64_t)a * ntr + otr, b->frac32 + (int64_t)a * b->n_tile_rows,
-                             sizeof(float) * b->n_tile_rows, hipMemcpyDeviceToDevice, st));
+      CPM_HIP(hipMemcpyAsync(c->slot_frac64 + a * ns + os, b->slot_frac64 + a * b->n_slots,
+                             sizeof(double2) * b->n_slots, hipMemcpyDeviceToDevice, st));
+      CPM_HIP(hipMemcpyAsync(c->slot_frac32 + a * ns + os, b->slot_frac32 + a * b->n_slots,
+                             sizeof(float2) * b->n_slots, hipMemcpyDeviceToDevice, st));
     }
-    CPM_HIP(hipMemcpyAsync(c->lbase + otr, b->lbase, sizeof(unsigned) * b->n_tile_rows,
+    CPM_HIP(hipMemcpyAsync(c->slot_base + os, b->slot_base, sizeof(unsigned short) * b->n_slots,
                            hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_cat_int, g(b->n_erows), dim3(256), 0, st, b->erow_id, c->erow_id + oe,
                        (int64_t)b->n_erows, add);
     hipLaunchKernelGGL(k_cat_int, g((int64_t)b->n_erows * nm), dim3(256), 0, st, b->ecol,
                        c->ecol + oe * nm, (int64_t)b->n_erows * nm, add);
     CPM_HIP(hipMemcpyAsync(c->ew + oe * nm, b->ew, sizeof(double) * b->n_erows * nm,
-                           hipMemcpyDeviceToDevice, st));
-    CPM_HIP(hipMemcpyAsync(c->ew32 + oe * nm, b->ew32, sizeof(float) * b->n_erows * nm,
                            hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_cat_int, g(b->n_lrows), dim3(256), 0, st, b->lrow_id, c->lrow_id + ol,
                        (int64_t)b->n_lrows, add);
@@ -424,19 +442,15 @@ void build_composite(cpm_batch* B, hipStream_t st) {
                        (int64_t)b->n_lrows, i);
     hipLaunchKernelGGL(k_fill_int, g(b->n_erows), dim3(256), 0, st, c->erow_inst + oe,
                        (int64_t)b->n_erows, i);
-    hipLaunchKernelGGL(k_fill_int, g(b->ntiles), dim3(256), 0, st, c->tile_inst + ot,
-                       (int64_t)b->ntiles, i);
     CPM_LAUNCH_CHECK();
-    B->h_boff[i] = (int)ob;
-    B->h_loff[i] = (int)ol;
-    ob += b->nb;
-    ot += b->ntiles;
-    otr += b->n_tile_rows;
+    B->h_boff[i] = (int)(ob / kBlkPad);
+    B->h_loff[i] = (int)(ol / kRowPad);
+    ob += up(b->nb, kBlkPad);
+    ot += b->nst;
+    os += b->n_slots;
     oe += b->n_erows;
-    ol += b->n_lrows;
+    ol += up(b->n_lrows, kRowPad);
   }
-  const int ntr32 = (int)ntr;
-  CPM_HIP(hipMemcpyAsync(c->tile_start + nt, &ntr32, sizeof(int), hipMemcpyHostToDevice, st));
   std::vector<double> coef(2 * ni);
   for (int i = 0; i < ni; ++i) {
     const double N2 = (double)B->bands[i]->N * (double)B->bands[i]->N;
@@ -445,8 +459,8 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   }
   CPM_HIP(hipMemcpyAsync(c->inst_coef, coef.data(), sizeof(double) * 2 * ni,
                          hipMemcpyHostToDevice, st));
-  B->h_boff[ni] = (int)ob;
-  B->h_loff[ni] = (int)ol;
+  B->h_boff[ni] = (int)(ob / kBlkPad);
+  B->h_loff[ni] = (int)(ol / kRowPad);
   B->boff = dalloc<int>(B, ni + 1);
   B->loff = dalloc<int>(B, ni + 1);
   CPM_HIP(hipMemcpyAsync(B->boff, B->h_boff.data(), sizeof(int) * (ni + 1),
@@ -531,8 +545,8 @@ struct BBicg {
     part = (double*)band_scratch(c, slot0 + 6, sizeof(double) * 2 * B->nchunks);
     S = (BScal*)band_scratch(c, slot0 + 7, sizeof(BScal) * B->nsys);
     act = (int*)band_scratch(c, slot0 + 8, sizeof(int) * B->nsys);
-    dnp = apply_dot_parts(c, false, sizeof(T) == 4);
-    lp0 = dnp - 128 * (c->n_lrows ? grid_for(c->n_lrows, 128) : 0);
+    dnp = apply_dot_parts(c, false);
+    lp0 = B->h_loff[B->ninst];
     dpart = (double*)band_scratch(c, slot0 + 9, sizeof(double) * 2 * (size_t)dnp * B->nrhs);
     CPM_HIP(hipMemsetAsync(S, 0, sizeof(BScal) * B->nsys, st));
     band_scratch(c, 0, apply_scratch_bytes(c, B->nrhs));

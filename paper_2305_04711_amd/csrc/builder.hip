@@ -507,6 +507,88 @@ __global__ void k_nonzero(const int* in, int n, int* out) {
   if (i < n) out[i] = in[i] > 0 ? 1 : 0;
 }
 
+// Supertiles: cells of 2 x 2 blocks in x and y (aligned in the grid of twice
+// the block size).  Blocks are in Morton order, so a cell's blocks, their
+// buckets of tile rows and the slots made from them are contiguous.
+__global__ void k_st_head(int nb, const int4* coord, int* head) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= nb) return;
+  const int4 c = coord[b];
+  bool h = b == 0;
+  if (!h) {
+    const int4 q = coord[b - 1];
+    h = (c.x >> 1) != (q.x >> 1) || (c.y >> 1) != (q.y >> 1) || c.z != q.z;
+  }
+  head[b] = h ? 1 : 0;
+}
+
+__global__ void k_st_first(int nb, const int* head, const int* sid, int* first) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < nb && head[b]) first[sid[b]] = b;
+}
+
+// slots of a bucket of cnt rows
+__global__ void k_slot_counts(int64_t nbk, const int* cnt, int* slots) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < nbk) slots[k] = (cnt[k] + 1) >> 1;
+}
+
+// 1 for the cells that hold slots; slot0 has nb * 64 + 1 entries
+__global__ void k_st_used(int ncell, const int* first, const int* slot0, int* used) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < ncell) used[s] = slot0[(int64_t)first[s + 1] * 64] > slot0[(int64_t)first[s] * 64];
+}
+
+// ranges and staged blocks of the supertiles (cells with slots)
+template <int DIM>
+__global__ void k_st_fill(Blocks B, int ncell, const int* first, const int* slot0,
+                          const int* used, const int* idx, int4* rng, QMeta* meta) {
+  constexpr int NQ = DIM == 3 ? 18 : 9;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= (int64_t)ncell * NQ) return;
+  const int s = (int)(g / NQ), q = (int)(g % NQ);
+  if (!used[s]) return;
+  const int4 c = B.coord[first[s]];
+  const int bx = (c.x & ~1) + q % 3, by = (c.y & ~1) + (q / 3) % 3,
+            bz = c.z + q / 9;
+  const int id = hash_find(B.hkeys, B.hvals, B.hcap, block_key(bx, by, bz));
+  meta[(int64_t)idx[s] * NQ + q] = id >= 0 ? QMeta{B.mask[id], B.off[id], id} : QMeta{0ull, 0, -1};
+  if (q == 0) {
+    const int s0 = slot0[(int64_t)first[s] * 64];
+    rng[idx[s]] = make_int4(s0, slot0[(int64_t)first[s + 1] * 64] - s0, 0, 0);
+  }
+}
+
+// The rows of a bucket (block of the stencil base, local base; ascending by
+// DOF) into its slots, two at a time.
+template <int DIM>
+__global__ void k_slot_fill(int64_t nbk, const int* cnt, const int* end, const int* slot0,
+                            const int4* coord, int ntr, const int* perm, const double* frac64,
+                            int64_t ns, int2* dof, unsigned short* base, double2* f64,
+                            float2* f32) {
+  using G = Geo<DIM>;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nbk;
+       k += (int64_t)gridDim.x * blockDim.x) {
+    const int n = cnt[k];
+    if (!n) continue;
+    const int r0 = end[k] - n, s0 = slot0[k];
+    const int4 c = coord[k >> 6];
+    const int code = (int)(k & 63);
+    const int lx = G::lx(code) + G::BX * (c.x & 1), ly = G::ly(code) + G::BX * (c.y & 1),
+              lz = DIM == 3 ? G::lz(code) : 0;
+    for (int j = 0; j < n; j += 2) {
+      const int i = r0 + j, i2 = j + 1 < n ? i + 1 : i, s = s0 + (j >> 1);
+      dof[s] = make_int2(perm[i], j + 1 < n ? perm[i2] : -1);
+      base[s] = (unsigned short)(lx | (ly << 4) | (lz << 8));
+      for (int a = 0; a < DIM; ++a) {
+        const double t0 = frac64[(int64_t)a * ntr + i], t1 = frac64[(int64_t)a * ntr + i2];
+        f64[a * ns + s] = make_double2(t0, t1);
+        f32[a * ns + s] = make_float2((float)t0, (float)t1);
+      }
+    }
+  }
+}
+
 // Explicit interpolation rows of swapped PDE rows.
 template <int DIM>
 __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64_t n_s,
@@ -1322,6 +1404,42 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       hipLaunchKernelGGL(k_tile_sort_buckets<DIM>, dim3(grid_for((int64_t)nb * 64, 256)),
                          dim3(256), 0, st, (int64_t)nb * 64, cnt2.p, pos2.p, ntr, b->perm,
                          b->frac64, b->frac32);
+      CPM_LAUNCH_CHECK();
+      // slots of two rows, and the supertiles that hold them
+      const int64_t nbk = (int64_t)nb * 64;
+      Tmp<int> nslot(b, nbk), slot0(b, nbk + 1);
+      hipLaunchKernelGGL(k_slot_counts, dim3((unsigned)((nbk + 255) / 256)), dim3(256), 0, st, nbk,
+                         cnt2.p, nslot.p);
+      CPM_LAUNCH_CHECK();
+      b->n_slots = scan_exclusive_i32(nslot.p, slot0.p, nbk, st, b->da);
+      const int ns32 = (int)b->n_slots;
+      CPM_HIP(hipMemcpyAsync(slot0.p + nbk, &ns32, sizeof(int), hipMemcpyHostToDevice, st));
+      Tmp<int> head(b, nb), sid(b, nb);
+      hipLaunchKernelGGL(k_st_head, dim3(grid_for(nb, 256)), dim3(256), 0, st, nb, b->blk_coord,
+                         head.p);
+      CPM_LAUNCH_CHECK();
+      const int ncell = (int)scan_exclusive_i32(head.p, sid.p, nb, st, b->da);
+      Tmp<int> first(b, (size_t)ncell + 1), used(b, ncell), idx(b, ncell);
+      CPM_HIP(hipMemcpyAsync(first.p + ncell, &nb, sizeof(int), hipMemcpyHostToDevice, st));
+      hipLaunchKernelGGL(k_st_first, dim3(grid_for(nb, 256)), dim3(256), 0, st, nb, head.p, sid.p,
+                         first.p);
+      hipLaunchKernelGGL(k_st_used, dim3(grid_for(ncell, 256)), dim3(256), 0, st, ncell, first.p,
+                         slot0.p, used.p);
+      CPM_LAUNCH_CHECK();
+      b->nst = (int)scan_exclusive_i32(used.p, idx.p, ncell, st, b->da);
+      constexpr int NQ = DIM == 3 ? 18 : 9;
+      b->st_meta = b->alloc<QMeta>((size_t)b->nst * NQ);
+      b->st_rng = b->alloc<int4>(b->nst);
+      b->slot_dof = b->alloc<int2>(b->n_slots);
+      b->slot_base = b->alloc<unsigned short>(b->n_slots);
+      b->slot_frac64 = b->alloc<double2>((size_t)DIM * b->n_slots);
+      b->slot_frac32 = b->alloc<float2>((size_t)DIM * b->n_slots);
+      hipLaunchKernelGGL(k_st_fill<DIM>, dim3((unsigned)(((int64_t)ncell * NQ + 255) / 256)),
+                         dim3(256), 0, st, B, ncell, first.p, slot0.p, used.p, idx.p, b->st_rng,
+                         b->st_meta);
+      hipLaunchKernelGGL(k_slot_fill<DIM>, dim3(grid_for(nbk, 256)), dim3(256), 0, st, nbk, cnt2.p,
+                         pos2.p, slot0.p, b->blk_coord, ntr, b->perm, b->frac64, b->n_slots,
+                         b->slot_dof, b->slot_base, b->slot_frac64, b->slot_frac32);
       CPM_LAUNCH_CHECK();
       CPM_HIP(hipStreamSynchronize(st));
     }

@@ -101,33 +101,20 @@ struct QMeta {
 
 // Launch variants of the apply kernels (chosen by the autotuner).
 struct Tune {
-  int pad = 1;     // LDS x-line stride of the staged cube: 0 -> E + 1, 1 -> E + 4
-  int xcd = 1;     // map consecutive tiles / blocks to one XCD
-  int ps = 0;      // tile gather as persistent wavefronts (implies xcd): 1
-                   // prefetches the next tile's metadata, 2 also its staging
-  int lap = 0;     // Laplacian pass: 0 gathers every neighbour, 1 exchanges
-                   // in-block neighbours between lanes, 2 does so in
-                   // persistent wavefronts that request the next block early,
-                   // 3 keeps the metadata in scalar registers and exchanges
-                   // with row moves and lane permutes (k_lap_w)
+  int pad = 1;     // LDS x-line padding of the staged cube (elements)
+  int xcd = 1;     // map consecutive supertiles / blocks to one XCD
   int tuned = 0;
 };
-// variant k: pad = k & 1, order mode = (k >> 1) & 3 (0 block order, 1
-// XCD-aware, 2 persistent XCD-aware gather, 3 persistent and pipelined),
-// lap = k >> 3
+// variant k: pad = k & 1, order = (k >> 1) & 3 (0 block order, else one
+// contiguous range per XCD); the higher bits select nothing any more
 constexpr int kTuneVariants = 32;
 inline Tune tune_variant(int k) {
   Tune t;
   t.pad = k & 1;
-  const int mode = (k >> 1) & 3;
-  t.xcd = mode != 0;
-  t.ps = mode >= 2 ? mode - 1 : 0;
-  t.lap = k >> 3;
+  t.xcd = ((k >> 1) & 3) != 0;
   t.tuned = 1;
   return t;
 }
-// Persistent tile gather: wavefronts per XCD (8 per SIMD at most are resident)
-constexpr int kPersistWavesPerXcd = 4096;
 
 }  // namespace cpm
 
@@ -176,6 +163,20 @@ struct cpm_band {
   int4* tile_col = nullptr;           // [ntiles]
   int col_start[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 
+  // supertiles: the tile rows whose stencil bases lie in 2 x 2 neighbouring
+  // blocks (x and y), two rows of one stencil base to a slot.  Slots are grouped by
+  // supertile, in it by tile and base; the rows of a base ascend by DOF, an
+  // odd last one is alone in its slot (second DOF -1, fraction repeated)
+  int nst = 0;
+  int64_t n_slots = 0;
+  cpm::QMeta* st_meta = nullptr;      // [nst][18, 2-D: 9] staged blocks
+  int4* st_rng = nullptr;             // [nst] first slot, slots, instance, 0
+  int2* slot_dof = nullptr;           // [n_slots]
+  unsigned short* slot_base = nullptr;   // [n_slots] stencil base from the supertile's
+                                      // corner, 4 bits per axis
+  double2* slot_frac64 = nullptr;     // [dim][n_slots]
+  float2* slot_frac32 = nullptr;      // [dim][n_slots]
+
   // rows with explicit interpolation stencils (swapped PDE rows, BC rows)
   int n_erows = 0;
   int* erow_id = nullptr;             // [n_erows]
@@ -215,7 +216,6 @@ struct cpm_band {
   double* inst_coef = nullptr;
   int* lrow_inst = nullptr;
   int* erow_inst = nullptr;           // instance of each explicit E row
-  int* tile_inst = nullptr;           // instance of each tile
   int* inst_skip = nullptr;           // [nrhs][instances] 1: skip (that system is done)
   int skip_stride = 0;                // instances (row length of inst_skip)
   bool composite = false;
@@ -258,19 +258,22 @@ size_t band_scratch_bytes(const cpm_band* b);
 // Its temporaries come from da.
 int64_t scan_exclusive_i32(const int* in, int* out, int64_t n, hipStream_t s, const DevAlloc& da);
 
-// apply entry points used by the solvers (nrhs = 1, optional gauge).  With
-// dy set, the kernel that writes v also writes the partials of (dy, v) and
-// (v, v) to dpart[0 .. np) and dpart[np .. 2 np), np = apply_dot_parts.
+// apply entry points used by the solvers (optional gauge).  With dy set, the
+// kernel that writes v also writes the partials of (dy, v) and (v, v) of
+// right-hand side r to dpart + 2 r np and np entries further, np =
+// apply_dot_parts.  done (optional, device): a flag that, set, turns the
+// launches into no-ops.
 template <class T>
 void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u,
                 T* v, hipStream_t s, const double* gauge_sum = nullptr,
-                double gamma = 0.0, const T* dy = nullptr, double* dpart = nullptr);
+                double gamma = 0.0, const T* dy = nullptr, double* dpart = nullptr,
+                const int* done = nullptr);
 template <class T>
 void apply_transpose_impl(const cpm_band* b, double m, double n, int nrhs,
                           const T* w, T* z, hipStream_t s,
                           const double* gauge_sum = nullptr, double gamma = 0.0,
                           const T* dy = nullptr, double* dpart = nullptr);
-int apply_dot_parts(const cpm_band* b, bool transpose, bool f32);
+int apply_dot_parts(const cpm_band* b, bool transpose);
 // bytes of the forward apply's scratch vector (the FP64 intermediate a = E u)
 size_t apply_scratch_bytes(const cpm_band* b, int nrhs);
 // out -= n (L - diag L) e(g): the Dirichlet part of a right-hand side

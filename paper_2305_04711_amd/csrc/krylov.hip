@@ -391,7 +391,7 @@ struct Bicg {
     t = (T*)band_scratch(b, slot0 + 5, vb);
     part = (double*)band_scratch(b, slot0 + 6, sizeof(double) * 2 * kMaxParts);
     S = (Scal*)band_scratch(b, slot0 + 7, sizeof(Scal));
-    dnp = apply_dot_parts(b, tr, sizeof(T) == 4);
+    dnp = apply_dot_parts(b, tr);
     dpart = (double*)band_scratch(b, slot0 + 8, sizeof(double) * 2 * (size_t)dnp);
     fin_g = (int)std::max<int64_t>(1, std::min<int64_t>(256, (dnp + 1023) / 1024));
     CPM_HIP(hipMemsetAsync(S, 0, sizeof(Scal), st));
