@@ -111,6 +111,10 @@ __device__ __forceinline__ void row_stencil(const TileView& tv, int pos, int lb[
 }
 
 // ---------------------------------------------------------------- pass 1
+__device__ __forceinline__ bool skipped(const Skip& s, int r, int inst) {
+  return s.f && s.f[(r * s.stride + inst) * s.elem];
+}
+
 // Sum over each aligned group of W lanes (16 or 64) by data-parallel
 // primitive moves, in a fixed order: quads, halves of a 16-lane row, rows,
 // then the four rows.  The sum is valid in every lane for W = 16 and in lane
@@ -153,9 +157,9 @@ template <int DIM> constexpr int erows_per_group() {
 template <class TS, int DIM>
 __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lane,
                                               const TS* __restrict__ u, double* __restrict__ a,
-                                              int64_t ld, int nrhs, const int* skip,
-                                              int skip_stride) {
+                                              int64_t ld, int nrhs, const Skip& skip) {
   constexpr int M = DIM == 3 ? 64 : 16, RPW = 64 / M;
+  if (!er.inst && nrhs == 1 && skipped(skip, 0, 0)) return;
   const int o = lane & (M - 1);
   int row[kERowPasses], c[kERowPasses];
   double w[kERowPasses];
@@ -179,7 +183,7 @@ __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lan
     for (int j = 0; j < kERowPasses; ++j) {
       const double s = lanes_sum<M>(v[j]);
       if (row[j] < 0 || o != M - 1) continue;
-      if (skip && skip[r * skip_stride + er.inst[row[j]]]) continue;
+      if (skipped(skip, r, er.inst ? er.inst[row[j]] : 0)) continue;
       a[r * ld + er.id[row[j]]] = s;
     }
   }
@@ -300,8 +304,7 @@ constexpr FaceLanes<DIM> face_lanes() {
 template <class TS, int DIM, int PAD, int NP>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_gather(
     ERows er, SuperView sv, const QMeta* __restrict__ meta, const int4* __restrict__ rng,
-    const TS* __restrict__ u, double* __restrict__ a, int64_t ld, int nrhs, int xcd,
-    const int* __restrict__ skip, int skip_stride, const int* __restrict__ done) {
+    const TS* __restrict__ u, double* __restrict__ a, int64_t ld, int nrhs, int xcd, Skip skip) {
   using G = Geo<DIM>;
   using SP = Super<DIM>;
   constexpr int EX = SP::EX, EP = EX + PAD, BX = G::BX, NB = SP::NB;
@@ -309,11 +312,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   constexpr int CS = SP::EZ * EX * EP;
   __shared__ double s_u[CS + 1];
   const int lane = threadIdx.x;
-  if (done && *done) return;
   int g = blockIdx.x;
   if (g < er.groups) {
     if (xcd) g = xcd_remap(g, er.groups);
-    explicit_rows<TS, DIM>(er, g, lane, u, a, ld, nrhs, skip, skip_stride);
+    explicit_rows<TS, DIM>(er, g, lane, u, a, ld, nrhs, skip);
     return;
   }
   g -= er.groups;
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   for (int r = 0; r < nrhs; ++r) {
     // keeps the cells of all staged blocks from living in registers throughout
     asm volatile("" : "+v"(cell0));
-    if (skip && skip[r * skip_stride + rg.z]) continue;
+    if (skipped(skip, r, rg.z)) continue;
     // the first pass's row data is requested before the staging loads
     rows(lane);
     __syncthreads();   // the previous right-hand side's rows are done
@@ -486,12 +488,11 @@ __global__ __launch_bounds__(256) void k_lap(
     LRows lr, const QMeta* __restrict__ face, int nb, const TU* __restrict__ u,
     const TA* __restrict__ a, TV* __restrict__ v, int64_t ld, int nrhs, double cd, double co,
     const double* __restrict__ gsum, double gscale, int xcd, const double* __restrict__ coef,
-    const int* __restrict__ skip, int skip_stride, DotOut<TV> dot, const int* __restrict__ done) {
+    Skip skip, DotOut<TV> dot) {
   using G = Geo<DIM>;
   constexpr int BX = G::BX, KB = kLapBlocksPerWave;
   constexpr int step[3] = {1, BX, BX * BX};
   constexpr FaceLanes<DIM> FL = face_lanes<DIM>();
-  if (done && *done) return;
   if (!ALL && (int)blockIdx.x < lr.groups) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int id = i < lr.n ? lr.id[i] : -1;
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(256) void k_lap(
     for (int f = 0; f < 2 * DIM; ++f) c[f] = id >= 0 ? lr.col[(int64_t)i * lr.nf + f] : -1;
     for (int r = 0; r < nrhs; ++r) {
       double d0 = 0.0, d1 = 0.0;
-      if (id >= 0 && !(skip && skip[r * skip_stride + inst])) {
+      if (id >= 0 && !skipped(skip, r, inst)) {
         double s = 0.0;
 #pragma unroll
         for (int f = 0; f < 2 * DIM; ++f)
@@ -577,7 +578,7 @@ __global__ __launch_bounds__(256) void k_lap(
   }
   const int zl = ((lane + step[DIM - 1]) & 63) << 2, zh = ((lane - step[DIM - 1]) & 63) << 2;
   for (int r = 0; r < nrhs; ++r) {
-    if (skip && skip[r * skip_stride + inst]) continue;
+    if (skipped(skip, r, inst)) continue;
     // Every load of the wave's blocks first, then the exchanges and sums.
     // Every lane loads (its own or, absent, its block's first value where it
     // has no neighbour across a face) and drops what it has no use for: under
@@ -1000,11 +1001,10 @@ static const Tune& tune_of(const cpm_band* b) {
 // What of a pass a launch does: all of it, or (measurement only) one part.
 enum { PART_ALL = 0, PART_MAIN = 1, PART_EXPLICIT = 2 };
 
-// a = E u for nrhs right-hand sides, in one launch.  skip (composites):
-// [nrhs][skip_stride] flags of systems to leave out.
+// a = E u for nrhs right-hand sides, in one launch.
 template <class T, int DIM>
 static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hipStream_t st,
-                          int part, const int* done) {
+                          int part, const Skip& skip) {
   const Tune& tn = tune_of<T>(b);
   constexpr int RG = erows_per_group<DIM>();
   ERows er{b->n_erows, (int)(((int64_t)b->n_erows + 8 * RG - 1) / (8 * RG)) * 8, b->erow_id,
@@ -1016,7 +1016,7 @@ static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hi
   if (!g) return;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(64), 0, st, er, sv, b->st_meta, b->st_rng, u, a, b->n, nrhs, tn.xcd,
-                       b->inst_skip, b->skip_stride, done);
+                       skip);
   };
   auto multi = [&](auto pad, auto np) { go(k_gather<T, DIM, pad(), np()>); };
   using I0 = std::integral_constant<int, 0>;
@@ -1050,14 +1050,14 @@ template <class TU, class TA, class TV, int DIM, bool ALL, bool DOT>
 static void launch_lap(const cpm_band* b, const Tune& tn, hipStream_t st, const TU* u,
                        const TA* a, TV* v, int64_t ld, int nrhs, double cd, double co,
                        const double* gsum, double gscale, const double* coef, DotOut<TV> dot,
-                       int part, const int* done) {
+                       int part, const Skip& skip) {
   LRows lr{b->n_lrows, ALL || part == PART_MAIN ? 0 : lap_row_groups(b), 2 * DIM, b->lrow_id,
            b->lcol, b->lrow_inst};
   const int64_t g = (int64_t)lr.groups + (part == PART_EXPLICIT ? 0 : lap_groups(b));
   if (!g) return;
   hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g), dim3(256), 0, st, lr,
                      b->blk_face, b->nb, u, a, v, ld, nrhs, cd, co, gsum, gscale, tn.xcd, coef,
-                     ALL ? nullptr : b->inst_skip, b->skip_stride, dot, done);
+                     skip, dot);
   CPM_LAUNCH_CHECK();
 }
 
@@ -1075,23 +1075,23 @@ template <class T, int DIM>
 static void apply_dim(const cpm_band* b, double m, double n, int nrhs, const T* u, T* v,
                       hipStream_t st, const double* gsum, double gamma, double* a,
                       hipEvent_t* ev = nullptr, const T* dy = nullptr, double* dpart = nullptr,
-                      const int* done = nullptr) {
+                      const Skip& skip = {}) {
   const int64_t ld = b->n;
   const double N2 = (double)b->N * (double)b->N;
   const double cd = m + n * (-2.0 * DIM * N2);
   const double co = n * N2;
   const double gscale = gsum ? gamma / (double)b->n_s : 0.0;
   const Tune& tn = tune_of<T>(b);
-  auto gather = [&](int part) { launch_gather<T, DIM>(b, nrhs, u, a, st, part, done); };
+  auto gather = [&](int part) { launch_gather<T, DIM>(b, nrhs, u, a, st, part, skip); };
   auto lap = [&](int part) {
     if (dy)
       launch_lap<T, double, T, DIM, false, true>(
           b, tn, st, u, a, v, ld, nrhs, cd, co, gsum, gscale, b->inst_coef,
-          DotOut<T>{dy, dpart, apply_dot_parts(b, false)}, part, done);
+          DotOut<T>{dy, dpart, apply_dot_parts(b, false)}, part, skip);
     else
       launch_lap<T, double, T, DIM, false, false>(b, tn, st, u, a, v, ld, nrhs, cd, co, gsum,
                                                   gscale, b->inst_coef,
-                                                  DotOut<T>{nullptr, nullptr, 0}, part, done);
+                                                  DotOut<T>{nullptr, nullptr, 0}, part, skip);
   };
   if (!ev) {
     gather(PART_ALL);
@@ -1119,7 +1119,7 @@ void apply_with_scratch(const cpm_band* b, double m, double n, int nrhs, const T
 template <class T>
 void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u, T* v, hipStream_t st,
                 const double* gauge_sum, double gamma, const T* dy, double* dpart,
-                const int* done) {
+                Skip skip) {
   double* gs = nullptr;
   if (gamma != 0.0) {
     // gauge: gamma * (sum of the PDE entries of u) / n_s on every row
@@ -1133,8 +1133,8 @@ void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u, T* 
     CPM_LAUNCH_CHECK();
   }
   double* a = static_cast<double*>(band_scratch(b, 0, apply_scratch_bytes(b, nrhs)));
-  if (b->dim == 3) apply_dim<T, 3>(b, m, n, nrhs, u, v, st, gs, gamma, a, nullptr, dy, dpart, done);
-  else apply_dim<T, 2>(b, m, n, nrhs, u, v, st, gs, gamma, a, nullptr, dy, dpart, done);
+  if (b->dim == 3) apply_dim<T, 3>(b, m, n, nrhs, u, v, st, gs, gamma, a, nullptr, dy, dpart, skip);
+  else apply_dim<T, 2>(b, m, n, nrhs, u, v, st, gs, gamma, a, nullptr, dy, dpart, skip);
 }
 
 // The transposed apply.  c = (L - diag L)^T w and e = E^T c are FP64 scratch
@@ -1157,7 +1157,7 @@ static void apply_T_dim(const cpm_band* b, double m, double n, int nrhs, const T
                          c + r * ld + b->n_s, (int64_t)b->n_c, 0.0);
   launch_lap<T, T, double, DIM, true, false>(b, tune_of<T>(b), st, w, w, c, ld, nrhs, 0.0, co,
                                              nullptr, 0.0, nullptr,
-                                             DotOut<double>{nullptr, nullptr, 0}, PART_ALL, nullptr);
+                                             DotOut<double>{nullptr, nullptr, 0}, PART_ALL, Skip{});
   if (b->lt_tgt) {
     if (b->n_lt) {
       hipLaunchKernelGGL(k_lt_pull<T>, dim3(grid_for(b->n_lt, 256)), dim3(256), 0, st, b->n_lt,
@@ -1215,11 +1215,9 @@ void apply_transpose_impl(const cpm_band* b, double m, double n, int nrhs, const
 }
 
 template void apply_impl<double>(const cpm_band*, double, double, int, const double*, double*,
-                                 hipStream_t, const double*, double, const double*, double*,
-                                const int*);
+                                 hipStream_t, const double*, double, const double*, double*, Skip);
 template void apply_impl<float>(const cpm_band*, double, double, int, const float*, float*,
-                                hipStream_t, const double*, double, const float*, double*,
-                                const int*);
+                                hipStream_t, const double*, double, const float*, double*, Skip);
 template void apply_transpose_impl<double>(const cpm_band*, double, double, int, const double*,
                                            double*, hipStream_t, const double*, double,
                                            const double*, double*);

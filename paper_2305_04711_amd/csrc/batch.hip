@@ -6,9 +6,8 @@
 // on it, with per-instance FD coefficients looked up through the instance id
 // stored in each block's metadata.  The Krylov solver is BiCGSTAB with one
 // set of scalars and one convergence flag per system (instance, right-hand
-// side): every reduction is segmented over fixed chunks of one system, and
-// the last workgroup of a system finishes that system's sums in a fixed
-// order.  Mixed precision works as for one band: FP32 BiCGSTAB for the
+// side): every reduction is segmented over fixed chunks of one system, whose
+// partials the next kernel adds up in a fixed order.  Mixed precision works as for one band: FP32 BiCGSTAB for the
 // correction inside FP64 iterative refinement, per system.
 #include <algorithm>
 #include <chrono>
@@ -23,11 +22,17 @@ struct BScal {
   double rho, rho_old, alpha, omega, beta;
   double bb, rr, tol2;
   int done, breakdown, it, active;
-  unsigned counter;
-  unsigned pad;
+  int fresh;      // no iteration since the start: beta = 0, no sums to add
+  int pad;
 };
 
-constexpr int kChunk = 32768;  // elements per reduction workgroup (256 x 128)
+// Elements per workgroup of the vector kernels: a system is cut into chunks,
+// the same for every system of a batch, between these bounds and so that the
+// batch has about kChunksWanted of them.  With 32768 for every batch six
+// instances of 0.1M to 0.4M DOFs gave 168 workgroups, fewer than the CUs, and
+// k_bxr took 92 us for 4.1M elements; each of a system's chunks adds up all of
+// its partials, so large systems take larger chunks.
+constexpr int kMinChunk = 2048, kMaxChunk = 32768, kChunksWanted = 4096;
 constexpr int kBT = 256;
 
 // ---------------------------------------------------------------- concat
@@ -79,56 +84,52 @@ struct Seg {
   const int* snch;       // [nsys] chunks of the system
 };
 
-template <int NR>
-__device__ __forceinline__ void bwg_sum(double v[NR], double (*sh)[kBT]) {
-  for (int k = 0; k < NR; ++k) sh[k][threadIdx.x] = v[k];
-  __syncthreads();
-  for (int o = kBT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o)
-      for (int k = 0; k < NR; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
-    __syncthreads();
+// Workgroup sums of v[0] and v[1], in every thread, in a fixed order.
+__device__ __forceinline__ void bwg_sum2(double v[2]) {
+  __shared__ double sh[2][kBT / 64];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = v[k];
   }
-  for (int k = 0; k < NR; ++k) v[k] = sh[k][0];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    v[k] = sh[k][0];
+    for (int w = 1; w < kBT / 64; ++w) v[k] += sh[k][w];
+  }
 }
 
-// Partial sums of this chunk; true in the last workgroup of the system, with
-// out[] the system's totals summed over its chunks in order.
-template <int NR>
-__device__ bool seg_finish(double v[NR], double* part, int nchunks, const Seg& g, int s,
-                           BScal* S, double out[NR]) {
-  __shared__ double sh[NR][kBT];
-  __shared__ bool last;
-  bwg_sum<NR>(v, sh);
+// This chunk's sums to its places in part ([2][nchunks]).
+__device__ __forceinline__ void seg_put(double v[2], double* part, int nchunks) {
+  bwg_sum2(v);
   if (threadIdx.x == 0) {
-    for (int k = 0; k < NR; ++k) part[(int64_t)k * nchunks + blockIdx.x] = v[k];
-    __threadfence();
-    const unsigned prev = atomicAdd(&S[s].counter, 1u);
-    last = (int)prev == g.snch[s] - 1;
+    part[blockIdx.x] = v[0];
+    part[nchunks + blockIdx.x] = v[1];
   }
-  __syncthreads();
-  if (!last) return false;
-  __threadfence();
-  double acc[NR];
-  for (int k = 0; k < NR; ++k) acc[k] = 0.0;
+}
+
+// The sums of system s over its chunks, in every thread.
+__device__ __forceinline__ void seg_add(const double* __restrict__ part, int nchunks, const Seg& g,
+                                        int s, double v[2]) {
+  v[0] = v[1] = 0.0;
   const int c0 = g.sfirst[s], nc = g.snch[s];
-  for (int c = threadIdx.x; c < nc; c += kBT)
-    for (int k = 0; k < NR; ++k)
-      acc[k] += __builtin_nontemporal_load(&part[(int64_t)k * nchunks + c0 + c]);
-  __syncthreads();
-  bwg_sum<NR>(acc, sh);
-  for (int k = 0; k < NR; ++k) out[k] = acc[k];
-  if (threadIdx.x == 0) S[s].counter = 0;
-  return true;
+  for (int c = threadIdx.x; c < nc; c += kBT) {
+    v[0] += part[c0 + c];
+    v[1] += part[nchunks + c0 + c];
+  }
+  bwg_sum2(v);
 }
 
 #define SEG_PROLOGUE                                  \
   const int s = g.csys[blockIdx.x];                   \
   const int64_t lo = g.clo[blockIdx.x], hi = g.chi[blockIdx.x]
 
+// r = b - v, rh = r, and the partials of (r, r), (b, b) of active systems
 template <class T>
 __global__ __launch_bounds__(256) void k_binit(int nchunks, Seg g, const T* __restrict__ b,
                                                const T* __restrict__ v, int has_v, T* r, T* rh,
-                                               T* p, double* part, BScal* S, double tol) {
+                                               double* part, const BScal* S) {
   SEG_PROLOGUE;
   if (!S[s].active) return;
   double acc[2] = {0.0, 0.0};
@@ -136,21 +137,89 @@ __global__ __launch_bounds__(256) void k_binit(int nchunks, Seg g, const T* __re
     const T ri = has_v ? b[i] - v[i] : b[i];
     r[i] = ri;
     rh[i] = ri;
-    p[i] = ri;
     acc[0] += (double)ri * (double)ri;
     acc[1] += (double)b[i] * (double)b[i];
   }
+  seg_put(acc, part, nchunks);
+}
+
+// one workgroup per system: its scalars at the start of the recurrence
+__global__ __launch_bounds__(256) void k_binit_fin(int nchunks, Seg g,
+                                                   const double* __restrict__ part, BScal* S,
+                                                   double tol, const BScal* counts) {
+  const int s = blockIdx.x;
+  BScal& q = S[s];
+  if (!q.active) return;
   double tot[2];
-  if (seg_finish<2>(acc, part, nchunks, g, s, S, tot) && threadIdx.x == 0) {
-    BScal& q = S[s];
-    q.rho = q.rho_old = q.rr = tot[0];
-    q.bb = tot[1];
-    q.tol2 = tol * tol * tot[1];
-    q.alpha = q.omega = 1.0;
-    q.beta = 0.0;
-    q.breakdown = 0;
-    q.done = tot[0] <= q.tol2 ? 1 : 0;
+  seg_add(part, nchunks, g, s, tot);
+  if (threadIdx.x != 0) return;
+  q.rho = q.rho_old = q.rr = tot[0];
+  q.bb = tot[1];
+  q.tol2 = tol * tol * tot[1];
+  q.alpha = q.omega = 1.0;
+  q.beta = 0.0;
+  q.breakdown = 0;
+  q.fresh = 1;
+  if (counts) q.it = counts[s].it;
+  q.done = tot[0] <= q.tol2 ? 1 : 0;
+}
+
+// The end of an iteration, from rho = (rh, r) and rr = (r, r) of its residual.
+__device__ __forceinline__ void b_end_iteration(BScal& q, double rho, double rr) {
+  q.it += 1;
+  q.rr = rr;
+  if (!__builtin_isfinite(rr)) {
+    q.breakdown = 1;
+    q.done = 1;
+  } else if (rr <= q.tol2) {
+    q.done = 1;
+  } else if (rho == 0.0 || q.omega == 0.0) {
+    q.breakdown = 1;
+    q.done = 1;
+  } else {
+    q.rho_old = q.rho;
+    q.rho = rho;
+    q.beta = (q.rho / q.rho_old) * (q.alpha / q.omega);
   }
+}
+
+// The scalars after the last iteration, for the host: one workgroup per
+// system, S0 -> H.
+__global__ __launch_bounds__(256) void k_bsettle(int nchunks, Seg g, const BScal* S0,
+                                                 const double* __restrict__ part, BScal* H) {
+  const int s = blockIdx.x;
+  BScal q = S0[s];
+  if (!q.done && !q.fresh) {
+    double tot[2];
+    seg_add(part, nchunks, g, s, tot);
+    b_end_iteration(q, tot[0], tot[1]);
+  }
+  if (threadIdx.x == 0) H[s] = q;
+}
+
+// Ends the previous iteration (its partials in part), then
+// p = r + beta (p - omega v), or p = r at the start.  Every chunk of a system
+// reads its scalars in S0; the first one hands them on to S1.
+template <class T>
+__global__ __launch_bounds__(256) void k_bp(int nchunks, Seg g, const T* __restrict__ r,
+                                            T* __restrict__ p, const T* __restrict__ v,
+                                            const BScal* __restrict__ S0, BScal* __restrict__ S1,
+                                            const double* __restrict__ part) {
+  SEG_PROLOGUE;
+  BScal q = S0[s];
+  if (!q.done && !q.fresh) {
+    double tot[2];
+    seg_add(part, nchunks, g, s, tot);
+    b_end_iteration(q, tot[0], tot[1]);
+  }
+  if ((int)blockIdx.x == g.sfirst[s] && threadIdx.x == 0) S1[s] = q;
+  if (q.done) return;
+  if (q.fresh) {
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) p[i] = r[i];
+    return;
+  }
+  const T be = (T)q.beta, om = (T)q.omega;
+  for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) p[i] = r[i] + be * (p[i] - om * v[i]);
 }
 
 template <class T>
@@ -173,7 +242,6 @@ template <int MODE>
 __global__ __launch_bounds__(256) void k_bdot_fin(int ninst, const double* __restrict__ dp,
                                                   int np, int lp0, const int* __restrict__ boff,
                                                   const int* __restrict__ loff, BScal* S) {
-  __shared__ double sh[2][kBT];
   const int s = blockIdx.x, r = s / ninst, i = s % ninst;
   if (S[s].done) return;
   const double* d = dp + (size_t)2 * r * np;
@@ -186,7 +254,7 @@ __global__ __launch_bounds__(256) void k_bdot_fin(int ninst, const double* __res
     v[0] += d[k];
     v[1] += d[np + k];
   }
-  bwg_sum<2>(v, sh);
+  bwg_sum2(v);
   if (threadIdx.x != 0) return;
   if (MODE == 0) {
     if (v[0] == 0.0 || !__builtin_isfinite(v[0])) {
@@ -200,15 +268,22 @@ __global__ __launch_bounds__(256) void k_bdot_fin(int ninst, const double* __res
   }
 }
 
+// x += alpha p + omega s, r = s - omega t, and the partials of (rh, r), (r, r);
+// a system's first chunk hands its scalars on from S1 to S0.
 template <class T, class TX>
 __global__ __launch_bounds__(256) void k_bxr(int nchunks, Seg g, TX* __restrict__ x,
                                              const T* __restrict__ p, const T* __restrict__ sv,
                                              const T* __restrict__ t, T* __restrict__ r,
-                                             const T* __restrict__ rh, double* part, BScal* S) {
+                                             const T* __restrict__ rh, double* part,
+                                             const BScal* __restrict__ S1,
+                                             BScal* __restrict__ S0) {
   SEG_PROLOGUE;
-  if (S[s].done) return;
-  const T om = (T)S[s].omega;
-  const TX alx = (TX)S[s].alpha, omx = (TX)S[s].omega;
+  BScal q = S1[s];
+  if (!q.done) q.fresh = 0;
+  if ((int)blockIdx.x == g.sfirst[s] && threadIdx.x == 0) S0[s] = q;
+  if (q.done) return;
+  const T om = (T)q.omega;
+  const TX alx = (TX)q.alpha, omx = (TX)q.omega;
   double acc[2] = {0.0, 0.0};
   for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) {
     const T si = sv[i];
@@ -218,42 +293,14 @@ __global__ __launch_bounds__(256) void k_bxr(int nchunks, Seg g, TX* __restrict_
     acc[0] += (double)rh[i] * (double)ri;
     acc[1] += (double)ri * (double)ri;
   }
-  double tot[2];
-  if (seg_finish<2>(acc, part, nchunks, g, s, S, tot) && threadIdx.x == 0) {
-    BScal& q = S[s];
-    q.it += 1;
-    q.rr = tot[1];
-    if (!__builtin_isfinite(tot[1])) {
-      q.breakdown = 1;
-      q.done = 1;
-    } else if (tot[1] <= q.tol2) {
-      q.done = 1;
-    } else if (tot[0] == 0.0 || q.omega == 0.0) {
-      q.breakdown = 1;
-      q.done = 1;
-    } else {
-      q.rho_old = q.rho;
-      q.rho = tot[0];
-      q.beta = (q.rho / q.rho_old) * (q.alpha / q.omega);
-    }
-  }
+  seg_put(acc, part, nchunks);
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void k_bp(int nchunks, Seg g, const T* __restrict__ r,
-                                            T* __restrict__ p, const T* __restrict__ v,
-                                            const BScal* S) {
-  SEG_PROLOGUE;
-  if (S[s].done) return;
-  const T be = (T)S[s].beta, om = (T)S[s].omega;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) p[i] = r[i] + be * (p[i] - om * v[i]);
-}
-
-// FP64 residual r = b - v per system, with (r, r) and (b, b)
+// FP64 residual r = b - v per system, with the partials of (r, r) and (b, b)
 __global__ __launch_bounds__(256) void k_bres64(int nchunks, Seg g, const double* __restrict__ b,
                                                 const double* __restrict__ v,
-                                                double* __restrict__ r, double* part, BScal* S) {
-  SEG_PROLOGUE;
+                                                double* __restrict__ r, double* part) {
+  const int64_t lo = g.clo[blockIdx.x], hi = g.chi[blockIdx.x];
   double acc[2] = {0.0, 0.0};
   for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) {
     const double ri = b[i] - v[i];
@@ -261,8 +308,15 @@ __global__ __launch_bounds__(256) void k_bres64(int nchunks, Seg g, const double
     acc[0] += ri * ri;
     acc[1] += b[i] * b[i];
   }
+  seg_put(acc, part, nchunks);
+}
+
+__global__ __launch_bounds__(256) void k_bres64_fin(int nchunks, Seg g,
+                                                    const double* __restrict__ part, BScal* S) {
+  const int s = blockIdx.x;
   double tot[2];
-  if (seg_finish<2>(acc, part, nchunks, g, s, S, tot) && threadIdx.x == 0) {
+  seg_add(part, nchunks, g, s, tot);
+  if (threadIdx.x == 0) {
     S[s].rr = tot[0];
     S[s].bb = tot[1];
   }
@@ -301,7 +355,7 @@ __global__ void k_bscal_reset(BScal* S, int nsys, const int* active) {
   S[s].done = active[s] ? 0 : 1;
   S[s].active = active[s];
   S[s].breakdown = 0;
-  S[s].counter = 0;
+  S[s].fresh = 1;
 }
 
 }  // namespace cpm
@@ -398,9 +452,6 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   c->lcol = c->alloc<int>((size_t)nl * nf);
   c->lrow_inst = c->alloc<int>(nl);
   c->erow_inst = c->alloc<int>(ne);
-  c->inst_skip = c->alloc<int>((size_t)ni * B->nrhs);
-  c->skip_stride = ni;
-  CPM_HIP(hipMemsetAsync(c->inst_skip, 0, sizeof(int) * ni * B->nrhs, st));
   CPM_HIP(hipMemsetAsync(c->lrow_id, 0xff, sizeof(int) * nl, st));
   c->inst_coef = c->alloc<double>((size_t)2 * ni);
   int64_t ob = 0, ot = 0, os = 0, oe = 0, ol = 0;
@@ -474,6 +525,8 @@ void build_composite(cpm_batch* B, hipStream_t st) {
 
   // segmented layout: system s = r * ninst + i
   B->nsys = ni * B->nrhs;
+  const int64_t want = (B->total * B->nrhs / kChunksWanted + kBT - 1) / kBT * kBT;
+  const int64_t chunk = std::max<int64_t>(kMinChunk, std::min<int64_t>(kMaxChunk, want));
   std::vector<int> csys, sfirst(B->nsys), snch(B->nsys);
   std::vector<int64_t> clo, chi;
   for (int r = 0; r < B->nrhs; ++r)
@@ -481,10 +534,10 @@ void build_composite(cpm_batch* B, hipStream_t st) {
       const int s = r * ni + i;
       const int64_t base = (int64_t)r * B->total + B->D[i], len = B->D[i + 1] - B->D[i];
       sfirst[s] = (int)csys.size();
-      for (int64_t o = 0; o < len; o += kChunk) {
+      for (int64_t o = 0; o < len; o += chunk) {
         csys.push_back(s);
         clo.push_back(base + o);
-        chi.push_back(base + std::min<int64_t>(len, o + kChunk));
+        chi.push_back(base + std::min<int64_t>(len, o + chunk));
       }
       snch[s] = (int)csys.size() - sfirst[s];
     }
@@ -524,7 +577,7 @@ struct BBicg {
   double* part;
   double* dpart;   // partials of the dot products fused into the applies
   int dnp = 0, lp0 = 0;
-  BScal* S;
+  BScal* S;        // [3][nsys]: S0, S1 (k_bp, k_bxr hand them on) and the host's
   int* act;
   PinnedB pin;
   std::vector<int> hact;
@@ -543,22 +596,26 @@ struct BBicg {
     s = (T*)band_scratch(c, slot0 + 4, vb);
     t = (T*)band_scratch(c, slot0 + 5, vb);
     part = (double*)band_scratch(c, slot0 + 6, sizeof(double) * 2 * B->nchunks);
-    S = (BScal*)band_scratch(c, slot0 + 7, sizeof(BScal) * B->nsys);
+    S = (BScal*)band_scratch(c, slot0 + 7, sizeof(BScal) * 3 * B->nsys);
     act = (int*)band_scratch(c, slot0 + 8, sizeof(int) * B->nsys);
     dnp = apply_dot_parts(c, false);
     lp0 = B->h_loff[B->ninst];
     dpart = (double*)band_scratch(c, slot0 + 9, sizeof(double) * 2 * (size_t)dnp * B->nrhs);
-    CPM_HIP(hipMemsetAsync(S, 0, sizeof(BScal) * B->nsys, st));
+    CPM_HIP(hipMemsetAsync(S, 0, sizeof(BScal) * 3 * B->nsys, st));
     band_scratch(c, 0, apply_scratch_bytes(c, B->nrhs));
     set_active(hact);
   }
   ~BBicg() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
   }
-  // out = A in; with dy, also the partials of (dy, out) and (out, out)
+  // out = A in, every right-hand side in one launch per kernel; with dy, also
+  // the partials of (dy, out) and (out, out), leaving out the systems that S1
+  // says are done
   void apply(const T* in, T* out, const T* dy = nullptr) {
+    Skip skip;
+    if (dy) skip = Skip{&S[B->nsys].done, B->ninst, (int)(sizeof(BScal) / sizeof(int))};
     apply_impl<T>(B->comp.get(), 0.0, 0.0, B->nrhs, in, out, st, nullptr, 0.0, dy,
-                  dy ? dpart : nullptr);
+                  dy ? dpart : nullptr, skip);
   }
   void set_active(const std::vector<int>& a) {
     hact = a;
@@ -571,25 +628,34 @@ struct BBicg {
       if constexpr (std::is_same<T, TX>::value) apply(x, v);
       else CPM_FAIL(CPM_E_INVALID, "internal: warm start of a mixed-type recurrence");
     }
+    start(rhs, x_zero ? 0 : 1, tol);
+  }
+  // r = rhs - v (or rhs) and the scalars of the active systems; the partials
+  // of the others stay as they are.  counts (optional): scalars that hold the
+  // iterations so far.
+  void start(const T* rhs, int has_v, double tol, const BScal* counts = nullptr) {
     hipLaunchKernelGGL(k_binit<T>, dim3(B->nchunks), dim3(kBT), 0, st, B->nchunks, seg_of(B), rhs,
-                       v, x_zero ? 0 : 1, r, rh, p, part, S, tol);
+                       v, has_v, r, rh, part, S);
+    hipLaunchKernelGGL(k_binit_fin, dim3(B->nsys), dim3(kBT), 0, st, B->nchunks, seg_of(B), part,
+                       S, tol, counts);
     CPM_LAUNCH_CHECK();
   }
   void iteration(TX* x) {
     const Seg g = seg_of(B);
     const int nc = B->nchunks;
     const int ns = B->nsys, ni = B->ninst;
+    BScal* S1 = S + ns;
+    hipLaunchKernelGGL(k_bp<T>, dim3(nc), dim3(kBT), 0, st, nc, g, r, p, v, S, S1, part);
     // the dot products (rh, v) and (s, t), (t, t) are fused into the applies
     apply(p, v, rh);
     hipLaunchKernelGGL(k_bdot_fin<0>, dim3(ns), dim3(kBT), 0, st, ni, dpart, dnp, lp0, B->boff,
-                       B->loff, S);
-    hipLaunchKernelGGL(k_bs<T>, dim3(nc), dim3(kBT), 0, st, nc, g, r, v, s, S);
+                       B->loff, S1);
+    hipLaunchKernelGGL(k_bs<T>, dim3(nc), dim3(kBT), 0, st, nc, g, r, v, s, S1);
     apply(s, t, s);
     hipLaunchKernelGGL(k_bdot_fin<1>, dim3(ns), dim3(kBT), 0, st, ni, dpart, dnp, lp0, B->boff,
-                       B->loff, S);
+                       B->loff, S1);
     hipLaunchKernelGGL((k_bxr<T, TX>), dim3(nc), dim3(kBT), 0, st, nc, g, x, p, s, t, r, rh, part,
-                       S);
-    hipLaunchKernelGGL(k_bp<T>, dim3(nc), dim3(kBT), 0, st, nc, g, r, p, v, S);
+                       S1, S);
     CPM_LAUNCH_CHECK();
   }
   void run(TX* x, int k, bool graph) {
@@ -619,8 +685,13 @@ struct BBicg {
     }
     CPM_HIP(hipGraphLaunch(gexec, st));
   }
+  // the scalars after the iterations so far
   const BScal* read() {
-    CPM_HIP(hipMemcpyAsync(pin.h, S, sizeof(BScal) * B->nsys, hipMemcpyDeviceToHost, st));
+    BScal* H = S + 2 * B->nsys;
+    hipLaunchKernelGGL(k_bsettle, dim3(B->nsys), dim3(kBT), 0, st, B->nchunks, seg_of(B), S, part,
+                       H);
+    CPM_LAUNCH_CHECK();
+    CPM_HIP(hipMemcpyAsync(pin.h, H, sizeof(BScal) * B->nsys, hipMemcpyDeviceToHost, st));
     CPM_HIP(hipStreamSynchronize(st));
     return pin.h;
   }
@@ -645,14 +716,12 @@ struct BBicg {
       // refinement loop restarts it from the FP64 residual.
       if constexpr (std::is_same<T, TX>::value) if (any_rs && restarts < 50) {
         ++restarts;
-        clear_skip();   // the restart's apply must cover every instance
         const std::vector<int> keep = hact;
         set_active(rs);
         hipLaunchKernelGGL(k_bset_active, dim3((B->nsys + 127) / 128), dim3(128), 0, st, S,
                            B->nsys, act);
-        apply(x, v);
-        hipLaunchKernelGGL(k_binit<T>, dim3(B->nchunks), dim3(kBT), 0, st, B->nchunks, seg_of(B),
-                           rhs, v, 1, r, rh, p, part, S, tol);
+        apply(x, v);    // covers every system, whatever its state
+        start(rhs, 1, tol, S + 2 * B->nsys);
         set_active(keep);
         hipLaunchKernelGGL(k_bset_active, dim3((B->nsys + 127) / 128), dim3(128), 0, st, S,
                            B->nsys, act);
@@ -661,33 +730,11 @@ struct BBicg {
         continue;
       }
       if (all || it >= maxit) break;
-      update_skip(h);
       run(x, std::min(ce, maxit - it), graph && std::min(ce, maxit - it) == ce);
       h = read();
     }
-    clear_skip();
     return it;
   }
-  // converged systems (instance, right-hand side) are skipped by the apply
-  // kernels, which run one launch per right-hand side (system q = r * ninst
-  // + i is flag q)
-  void update_skip(const BScal* h) {
-    std::vector<int> sk(B->nsys, 1);
-    for (int q = 0; q < B->nsys; ++q)
-      if (!h[q].done) sk[q] = 0;
-    if (sk != hskip) {
-      hskip = sk;
-      CPM_HIP(hipMemcpyAsync(B->comp->inst_skip, hskip.data(), sizeof(int) * B->nsys,
-                             hipMemcpyHostToDevice, st));
-      CPM_HIP(hipStreamSynchronize(st));
-    }
-  }
-  void clear_skip() {
-    hskip.assign(B->nsys, 0);
-    CPM_HIP(hipMemsetAsync(B->comp->inst_skip, 0, sizeof(int) * B->nsys, st));
-    CPM_HIP(hipStreamSynchronize(st));
-  }
-  std::vector<int> hskip;
 };
 
 }  // namespace
@@ -793,7 +840,8 @@ extern "C" cpm_status cpm_batch_solve(cpm_batch* b, const cpm_solve_opts* o, con
     auto residual = [&]() {
       apply_impl<double>(c, 0.0, 0.0, b->nrhs, x, v64, st);
       hipLaunchKernelGGL(k_bres64, dim3(b->nchunks), dim3(kBT), 0, st, b->nchunks, seg_of(b), rhs,
-                         v64, r64, part, S);
+                         v64, r64, part);
+      hipLaunchKernelGGL(k_bres64_fin, dim3(ns), dim3(kBT), 0, st, b->nchunks, seg_of(b), part, S);
       CPM_LAUNCH_CHECK();
       CPM_HIP(hipMemcpyAsync(pin.h, S, sizeof(BScal) * ns, hipMemcpyDeviceToHost, st));
       CPM_HIP(hipStreamSynchronize(st));

@@ -216,8 +216,6 @@ struct cpm_band {
   double* inst_coef = nullptr;
   int* lrow_inst = nullptr;
   int* erow_inst = nullptr;           // instance of each explicit E row
-  int* inst_skip = nullptr;           // [nrhs][instances] 1: skip (that system is done)
-  int skip_stride = 0;                // instances (row length of inst_skip)
   bool composite = false;
 
   int64_t on_c_nodes = 0, no_bc_dof_swaps = 0;
@@ -258,16 +256,22 @@ size_t band_scratch_bytes(const cpm_band* b);
 // Its temporaries come from da.
 int64_t scan_exclusive_i32(const int* in, int* out, int64_t n, hipStream_t s, const DevAlloc& da);
 
+// Device flags of systems (right-hand side r, instance i) that a launch leaves
+// out: f[(r * stride + i) * elem] != 0; f null leaves none out.
+struct Skip {
+  const int* f = nullptr;
+  int stride = 1, elem = 1;
+};
+
 // apply entry points used by the solvers (optional gauge).  With dy set, the
 // kernel that writes v also writes the partials of (dy, v) and (v, v) of
 // right-hand side r to dpart + 2 r np and np entries further, np =
-// apply_dot_parts.  done (optional, device): a flag that, set, turns the
-// launches into no-ops.
+// apply_dot_parts; those of a system that is skipped are not written.
 template <class T>
 void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u,
                 T* v, hipStream_t s, const double* gauge_sum = nullptr,
                 double gamma = 0.0, const T* dy = nullptr, double* dpart = nullptr,
-                const int* done = nullptr);
+                Skip skip = {});
 template <class T>
 void apply_transpose_impl(const cpm_band* b, double m, double n, int nrhs,
                           const T* w, T* z, hipStream_t s,

@@ -5,11 +5,14 @@
 // true residual), finished in FP64 where FP32 stops making progress.
 //
 // The recurrence scalars live in device memory.  Every reduction kernel
-// writes one partial sum per workgroup; the last workgroup to finish (found
-// with a device-scope fence and an atomic counter) adds the partials in a
-// fixed order and updates the scalars, so results are bitwise reproducible
-// and the host only reads the scalars every `check_every` iterations.  The
-// check_every iterations can be captured once into a hipGraph and replayed.
+// writes one partial sum per workgroup, and the kernel that needs the sums
+// next adds them itself, each of its workgroups all of them in the same fixed
+// order, so results are bitwise reproducible and no kernel has to find its
+// last workgroup (a device-scope fence in every workgroup writes back the L2
+// of its XCD: the kernel that updates x and r took 41 us with such a finish
+// at 1.0M DOFs where the plain vector kernels take 6 to 7).  The host only
+// reads the scalars every `check_every` iterations.  The check_every
+// iterations can be captured once into a hipGraph and replayed.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -25,143 +28,241 @@ namespace cpm {
 struct Scal {
   double rho, rho_old, alpha, omega, beta;
   double bb, rr, tol2;
-  double d0, d1;
-  int done, breakdown, it, restarts;
-  unsigned counter;
-  unsigned pad;
+  int done, breakdown, it;
+  int fresh;      // no iteration since the start: beta = 0, no sums to add
 };
 
+// Scalars of one recurrence.  A kernel whose workgroups all read the scalars
+// must not have one of them overwrite what the others read, so an iteration
+// hands them on: k_p reads [0] and writes [1], k_s reads [1] and writes [2],
+// k_xr reads [2] and writes [0]; [3] is what the host reads.
+constexpr int kScalSlots = 4;
+
+// Copies field by field: a copy of the whole struct goes through a stack slot
+// per thread, which the compiler then keeps in LDS (12 KB a workgroup).
+__device__ __forceinline__ Scal get_scal(const Scal* S) {
+  Scal q;
+  q.rho = S->rho, q.rho_old = S->rho_old, q.alpha = S->alpha, q.omega = S->omega, q.beta = S->beta;
+  q.bb = S->bb, q.rr = S->rr, q.tol2 = S->tol2;
+  q.done = S->done, q.breakdown = S->breakdown, q.it = S->it, q.fresh = S->fresh;
+  return q;
+}
+
+__device__ __forceinline__ void set_scal(Scal* S, const Scal& q) {
+  S->rho = q.rho, S->rho_old = q.rho_old, S->alpha = q.alpha, S->omega = q.omega, S->beta = q.beta;
+  S->bb = q.bb, S->rr = q.rr, S->tol2 = q.tol2;
+  S->done = q.done, S->breakdown = q.breakdown, S->it = q.it, S->fresh = q.fresh;
+}
+
+// Vector kernels: four or more elements a thread, at most 1024 workgroups,
+// also those that write no partials, since each workgroup adds up the
+// partials of the kernel before it (0.26M DOFs: 72.7 us an iteration, against
+// 74.4 with up to 4096 workgroups of one element a thread).
 constexpr int kRedThreads = 256;
 constexpr int kMaxParts = 1024;
+// Partials that every workgroup of a consumer adds up by itself; more are
+// added by k_parts to kFoldParts first.  A sum over 2048 pairs reads 32 KB
+// from the L2 in about 2 us, less than another launch (5 us).
+constexpr int kDirectParts = 2048;
+constexpr int kFoldParts = 256;
 
 static int red_grid(int64_t n) {
   int64_t g = (n + kRedThreads * 4 - 1) / (kRedThreads * 4);
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxParts));
 }
 
-// Workgroup sum of NR values; thread 0 gets the totals.
-template <int NR>
-__device__ __forceinline__ void wg_sum(double v[NR], double (*sh)[kRedThreads]) {
-  for (int k = 0; k < NR; ++k) sh[k][threadIdx.x] = v[k];
-  __syncthreads();
-  for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o)
-      for (int k = 0; k < NR; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
-    __syncthreads();
+// Workgroup sums of v[0] and v[1], in every thread, in a fixed order.
+__device__ __forceinline__ void wg_sum2(double v[2]) {
+  __shared__ double sh[2][kRedThreads / 64];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = v[k];
   }
-  for (int k = 0; k < NR; ++k) v[k] = sh[k][0];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    v[k] = sh[k][0];
+    for (int w = 1; w < kRedThreads / 64; ++w) v[k] += sh[k][w];
+  }
 }
 
-// Writes this workgroup's partials; returns true in every thread of the last
-// workgroup, with out[] holding the grand totals (fixed summation order).
-template <int NR>
-__device__ bool finish_reduction(double v[NR], double* part, Scal* S, double out[NR]) {
-  __shared__ double sh[NR][kRedThreads];
-  __shared__ bool last;
-  wg_sum<NR>(v, sh);
+// This workgroup's sums to part[blockIdx.x] and part[ld + blockIdx.x].
+__device__ __forceinline__ void put_parts(double v[2], double* part, int ld) {
+  wg_sum2(v);
   if (threadIdx.x == 0) {
-    for (int k = 0; k < NR; ++k) part[k * kMaxParts + blockIdx.x] = v[k];
-    __threadfence();
-    const unsigned prev = atomicAdd(&S->counter, 1u);
-    last = prev == gridDim.x - 1;
+    part[blockIdx.x] = v[0];
+    part[ld + blockIdx.x] = v[1];
   }
-  __syncthreads();
-  if (!last) return false;
-  __threadfence();
-  double acc[NR];
-  for (int k = 0; k < NR; ++k) acc[k] = 0.0;
-  for (int i = threadIdx.x; i < (int)gridDim.x; i += kRedThreads)
-    for (int k = 0; k < NR; ++k) acc[k] += __builtin_nontemporal_load(&part[k * kMaxParts + i]);
-  __syncthreads();
-  wg_sum<NR>(acc, sh);
-  for (int k = 0; k < NR; ++k) out[k] = acc[k];
-  if (threadIdx.x == 0) S->counter = 0;
-  return true;
 }
 
-// r = b - v;  rh = r;  p = r;  sums (rh, r), (r, r), (b, b)
+// Sums of part[0 .. np) and part[ld .. ld + np), the same in every thread of
+// every workgroup.
+__device__ __forceinline__ void add_parts(const double* __restrict__ part, int ld, int np,
+                                          double v[2]) {
+  v[0] = v[1] = 0.0;
+  for (int i = threadIdx.x; i < np; i += kRedThreads) {
+    v[0] += part[i];
+    v[1] += part[ld + i];
+  }
+  wg_sum2(v);
+}
+
+// Partials of (y, v), (v, v) folded into kFoldParts of each.
+__global__ __launch_bounds__(256) void k_parts(const double* __restrict__ in, int np,
+                                               double* __restrict__ out, const Scal* S) {
+  if (S->done) return;
+  double acc[2] = {0.0, 0.0};
+  for (int i = blockIdx.x * kRedThreads + threadIdx.x; i < np; i += gridDim.x * kRedThreads) {
+    acc[0] += in[i];
+    acc[1] += in[np + i];
+  }
+  put_parts(acc, out, kFoldParts);
+}
+
+// r = b - v;  rh = r;  partials of (r, r), (b, b)
 template <class T>
 __global__ __launch_bounds__(256) void k_init(int64_t n, const T* __restrict__ b, const T* __restrict__ v,
-                                              bool has_v, T* r, T* rh, T* p, double* part, Scal* S,
-                                              double tol) {
+                                              bool has_v, T* r, T* rh, double* part) {
   double acc[2] = {0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kRedThreads) {
     const T ri = has_v ? b[i] - v[i] : b[i];
     r[i] = ri;
     rh[i] = ri;
-    p[i] = ri;
     const double d = (double)ri, bd = (double)b[i];
     acc[0] += d * d;
     acc[1] += bd * bd;
   }
+  put_parts(acc, part, kMaxParts);
+}
+
+__global__ __launch_bounds__(256) void k_init_fin(const double* __restrict__ part, int np, Scal* S,
+                                                  double tol) {
   double tot[2];
-  if (finish_reduction<2>(acc, part, S, tot) && threadIdx.x == 0) {
-    S->rho = tot[0];
-    S->rho_old = tot[0];
-    S->rr = tot[0];
-    S->bb = tot[1];
-    S->tol2 = tol * tol * tot[1];
-    S->alpha = S->omega = 1.0;
-    S->beta = 0.0;
-    S->breakdown = 0;
-    S->done = (tot[0] <= S->tol2) ? 1 : 0;
+  add_parts(part, kMaxParts, np, tot);
+  if (threadIdx.x != 0) return;
+  S->rho = tot[0];
+  S->rho_old = tot[0];
+  S->rr = tot[0];
+  S->bb = tot[1];
+  S->tol2 = tol * tol * tot[1];
+  S->alpha = S->omega = 1.0;
+  S->beta = 0.0;
+  S->breakdown = 0;
+  S->fresh = 1;
+  S->done = (tot[0] <= S->tol2) ? 1 : 0;
+}
+
+// The end of an iteration, from rho = (rh, r) and rr = (r, r) of its residual.
+__device__ __forceinline__ void end_iteration(Scal& q, double rho, double rr) {
+  q.it += 1;
+  q.rr = rr;
+  if (!__builtin_isfinite(rr)) {
+    q.breakdown = 1;
+    q.done = 1;
+  } else if (rho == 0.0 || q.omega == 0.0) {
+    q.done = 1;
+    q.breakdown = rr <= q.tol2 ? 0 : 1;
+  } else {
+    // rho and beta are kept current also on the converging iteration
+    q.rho_old = q.rho;
+    q.rho = rho;
+    q.beta = (q.rho / q.rho_old) * (q.alpha / q.omega);
+    if (rr <= q.tol2) q.done = 1;
   }
 }
 
-// Finishes a dot product fused into the apply that produced v (partials of
-// (y, v) in dp[0 .. np) and of (v, v) in dp[np .. 2 np)).  MODE 0: y = rh,
-// alpha = rho / (rh, v).  MODE 1: y = s, v = t, omega = (t, s) / (t, t).
-template <int MODE>
-__global__ __launch_bounds__(256) void k_dot_fin(const double* __restrict__ dp, int np,
-                                                 double* part, Scal* S) {
-  if (S->done) return;
-  double acc[2] = {0.0, 0.0};
-  for (int i = blockIdx.x * kRedThreads + threadIdx.x; i < np; i += gridDim.x * kRedThreads) {
-    acc[0] += dp[i];
-    acc[1] += dp[np + i];
+// The scalars after the last iteration, for the host (and, with force, a
+// breakdown flagged in the recurrence itself: the test hook below).
+__global__ __launch_bounds__(256) void k_settle(Scal* S, const double* __restrict__ part, int np,
+                                                int force) {
+  Scal q = get_scal(S + 0);
+  if (!q.done && !q.fresh) {
+    double tot[2];
+    add_parts(part, kMaxParts, np, tot);
+    end_iteration(q, tot[0], tot[1]);
   }
-  double tot[2];
-  if (finish_reduction<2>(acc, part, S, tot) && threadIdx.x == 0) {
-    if (MODE == 0) {
-      if (tot[0] == 0.0 || !__builtin_isfinite(tot[0])) {
-        S->breakdown = 1;
-        S->done = 1;
-      } else {
-        S->alpha = S->rho / tot[0];
-      }
-    } else {
-      if (tot[1] == 0.0 || !__builtin_isfinite(tot[1])) {
-        S->omega = 0.0;
-      } else {
-        S->omega = tot[0] / tot[1];
-      }
-    }
+  if (threadIdx.x != 0) return;
+  if (force && !q.done) {
+    q.breakdown = 1;
+    q.done = 1;
+    set_scal(S + 0, q);
   }
+  set_scal(S + 3, q);
 }
 
-// s = r - alpha v
+// Ends the previous iteration (its partials in part), then
+// p = r + beta (p - omega v), or p = r at the start.
+template <class T>
+__global__ __launch_bounds__(256) void k_p(int64_t n, const T* __restrict__ r, T* __restrict__ p,
+                                           const T* __restrict__ v, Scal* S,
+                                           const double* __restrict__ part, int np) {
+  Scal q = get_scal(S + 0);
+  if (!q.done && !q.fresh) {
+    double tot[2];
+    add_parts(part, kMaxParts, np, tot);
+    end_iteration(q, tot[0], tot[1]);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) set_scal(S + 1, q);
+  if (q.done) return;
+  const T be = (T)q.beta, om = (T)q.omega;
+  if (q.fresh) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+      p[i] = r[i];
+    return;
+  }
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = r[i] + be * (p[i] - om * v[i]);
+}
+
+// alpha = rho / (rh, v) from the partials dp of (rh, v);  s = r - alpha v
 template <class T>
 __global__ __launch_bounds__(256) void k_s(int64_t n, const T* __restrict__ r, const T* __restrict__ v,
-                                           T* __restrict__ s, const Scal* S) {
-  if (S->done) return;
-  const T al = (T)S->alpha;
+                                           T* __restrict__ s, Scal* S,
+                                           const double* __restrict__ dp, int ld, int np) {
+  Scal q = get_scal(S + 1);
+  if (!q.done) {
+    double tot[2];
+    add_parts(dp, ld, np, tot);
+    if (tot[0] == 0.0 || !__builtin_isfinite(tot[0])) {
+      q.breakdown = 1;
+      q.done = 1;
+    } else {
+      q.alpha = q.rho / tot[0];
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) set_scal(S + 2, q);
+  if (q.done) return;
+  const T al = (T)q.alpha;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     s[i] = r[i] - al * v[i];
 }
 
-// x += alpha p + omega s;  r = s - omega t;  rho = (rh, r);  rr = (r, r).
+// omega = (t, s) / (t, t) from the partials dp;  x += alpha p + omega s;
+// r = s - omega t;  partials of rho = (rh, r), rr = (r, r).
 // The iterate x may be kept in a wider type TX than the recurrence vectors
 // (FP64 x with an FP32 recurrence: the update is not rounded to FP32).
 template <class T, class TX>
 __global__ __launch_bounds__(256) void k_xr(int64_t n, TX* __restrict__ x, const T* __restrict__ p,
                                             const T* __restrict__ s, const T* __restrict__ t,
                                             T* __restrict__ r, const T* __restrict__ rh,
-                                            double* part, Scal* S) {
-  if (S->done) return;
-  const T al = (T)S->alpha, om = (T)S->omega;
-  const TX alx = (TX)S->alpha, omx = (TX)S->omega;
+                                            Scal* S, const double* __restrict__ dp, int ld, int np,
+                                            double* __restrict__ part) {
+  Scal q = get_scal(S + 2);
+  if (!q.done) {
+    double tot[2];
+    add_parts(dp, ld, np, tot);
+    q.omega = (tot[1] == 0.0 || !__builtin_isfinite(tot[1])) ? 0.0 : tot[0] / tot[1];
+    q.fresh = 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) set_scal(S + 0, q);
+  if (q.done) return;
+  const T om = (T)q.omega;
+  const TX alx = (TX)q.alpha, omx = (TX)q.omega;
   double acc[2] = {0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kRedThreads) {
@@ -172,49 +273,15 @@ __global__ __launch_bounds__(256) void k_xr(int64_t n, TX* __restrict__ x, const
     acc[0] += (double)rh[i] * (double)ri;
     acc[1] += (double)ri * (double)ri;
   }
-  double tot[2];
-  if (finish_reduction<2>(acc, part, S, tot) && threadIdx.x == 0) {
-    S->it += 1;
-    S->rr = tot[1];
-    if (!__builtin_isfinite(tot[1])) {
-      S->breakdown = 1;
-      S->done = 1;
-    } else if (tot[0] == 0.0 || S->omega == 0.0) {
-      S->done = 1;
-      S->breakdown = tot[1] <= S->tol2 ? 0 : 1;
-    } else {
-      // rho and beta are kept current also on the converging iteration
-      S->rho_old = S->rho;
-      S->rho = tot[0];
-      S->beta = (S->rho / S->rho_old) * (S->alpha / S->omega);
-      if (tot[1] <= S->tol2) S->done = 1;
-    }
-  }
-}
-
-template <class T>
-__global__ void k_zero(int64_t n, T* __restrict__ x) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = T(0);
-}
-
-// p = r + beta (p - omega v)
-template <class T>
-__global__ __launch_bounds__(256) void k_p(int64_t n, const T* __restrict__ r, T* __restrict__ p,
-                                           const T* __restrict__ v, const Scal* S) {
-  if (S->done) return;
-  const T be = (T)S->beta, om = (T)S->omega;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = r[i] + be * (p[i] - om * v[i]);
+  __syncthreads();   // wg_sum2 used its shared sums above
+  put_parts(acc, part, kMaxParts);
 }
 
 // ---- mixed precision helpers (FP64 side)
-// r = b - v (FP64) and rr = (r, r), bb = (b, b)
+// r = b - v (FP64) and the partials of rr = (r, r), bb = (b, b)
 __global__ __launch_bounds__(256) void k_res64(int64_t n, const double* __restrict__ b,
                                                const double* __restrict__ v, double* __restrict__ r,
-                                               double* part, Scal* S) {
+                                               double* part) {
   double acc[2] = {0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kRedThreads) {
@@ -223,8 +290,13 @@ __global__ __launch_bounds__(256) void k_res64(int64_t n, const double* __restri
     acc[0] += ri * ri;
     acc[1] += b[i] * b[i];
   }
+  put_parts(acc, part, kMaxParts);
+}
+
+__global__ __launch_bounds__(256) void k_res64_fin(const double* __restrict__ part, int np, Scal* S) {
   double tot[2];
-  if (finish_reduction<2>(acc, part, S, tot) && threadIdx.x == 0) {
+  add_parts(part, kMaxParts, np, tot);
+  if (threadIdx.x == 0) {
     S->rr = tot[0];
     S->bb = tot[1];
   }
@@ -250,14 +322,6 @@ __global__ void k_scaleT(int64_t n, const double* __restrict__ r, double inv, T*
 }
 
 
-// Flags a breakdown of the recurrence (the test hook below).
-__global__ void k_force_breakdown(Scal* S) {
-  if (threadIdx.x == 0 && !S->done) {
-    S->breakdown = 1;
-    S->done = 1;
-  }
-}
-
 __global__ void k_set_it(Scal* S, int it) {
   if (threadIdx.x == 0) S->it = it;
 }
@@ -267,7 +331,6 @@ __global__ void k_zero_scal(Scal* S) {
     S->it = 0;
     S->done = 0;
     S->breakdown = 0;
-    S->counter = 0;
   }
 }
 
@@ -372,10 +435,11 @@ struct Bicg {
   T *r, *rh, *p, *v, *s, *t;
   double* part;
   double* dpart;   // partials of the dot products fused into the applies
-  int dnp, fin_g;
+  double* dfold;   // the same folded, where they are many
+  int dnp;
   Scal* S;
   Pinned pin;
-  int ew_grid, red_g;
+  int red_g;
   hipGraphExec_t gexec = nullptr;
   int graph_iters = 0;
   TX* gx_x = nullptr;
@@ -390,12 +454,11 @@ struct Bicg {
     s = (T*)band_scratch(b, slot0 + 4, vb);
     t = (T*)band_scratch(b, slot0 + 5, vb);
     part = (double*)band_scratch(b, slot0 + 6, sizeof(double) * 2 * kMaxParts);
-    S = (Scal*)band_scratch(b, slot0 + 7, sizeof(Scal));
+    S = (Scal*)band_scratch(b, slot0 + 7, sizeof(Scal) * kScalSlots);
     dnp = apply_dot_parts(b, tr);
     dpart = (double*)band_scratch(b, slot0 + 8, sizeof(double) * 2 * (size_t)dnp);
-    fin_g = (int)std::max<int64_t>(1, std::min<int64_t>(256, (dnp + 1023) / 1024));
-    CPM_HIP(hipMemsetAsync(S, 0, sizeof(Scal), st));
-    ew_grid = grid_for(n, 256, 4096);
+    dfold = (double*)band_scratch(b, slot0 + 9, sizeof(double) * 2 * kFoldParts);
+    CPM_HIP(hipMemsetAsync(S, 0, sizeof(Scal) * kScalSlots, st));
     red_g = red_grid(n);
     // make sure every scratch buffer exists before any graph capture
     band_scratch(b, 0, apply_scratch_bytes(b, 1));
@@ -412,15 +475,18 @@ struct Bicg {
     if (gexec) (void)hipGraphExecDestroy(gexec);
   }
 
-  // out = A in; with dy, also the partials of (dy, out) and (out, out)
-  void apply(const T* in, T* out, const T* dy = nullptr) {
+  // out = A in; with dy, also the partials of (dy, out) and (out, out), left
+  // out once the scalars q say that the recurrence has ended
+  void apply(const T* in, T* out, const T* dy = nullptr, const Scal* q = nullptr) {
     double* dp = dy ? dpart : nullptr;
     if (transpose) apply_transpose_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp);
-    else apply_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp);
+    else
+      apply_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp,
+                    Skip{q ? &q->done : nullptr, 1, 1});
   }
 
-  // r = rhs - A x, rh = p = r, v = 0, beta = 0 (so the first direction
-  // update of an iteration leaves p = r); x is read only when x_zero is false,
+  // r = rhs - A x, rh = r, and the scalars of a recurrence that starts there
+  // (its first direction is p = r); x is read only when x_zero is false,
   // which needs TX = T
   void init(const T* rhs, const TX* x, bool x_zero, double tol) {
     if (!x_zero) {
@@ -428,22 +494,30 @@ struct Bicg {
       else CPM_FAIL(CPM_E_INVALID, "internal: warm start of a mixed-type recurrence");
     }
     hipLaunchKernelGGL(k_init<T>, dim3(red_g), dim3(kRedThreads), 0, st, n, rhs, v, !x_zero, r,
-                       rh, p, part, S, tol);
-    hipLaunchKernelGGL(k_zero<T>, dim3(ew_grid), dim3(256), 0, st, n, v);
+                       rh, part);
+    hipLaunchKernelGGL(k_init_fin, dim3(1), dim3(kRedThreads), 0, st, part, red_g, S, tol);
     CPM_LAUNCH_CHECK();
   }
 
   // One BiCGSTAB step, starting with the direction update so that a step
   // ends right after the new residual (where an update can take place).
   void iteration(TX* x) {
-    hipLaunchKernelGGL(k_p<T>, dim3(ew_grid), dim3(256), 0, st, n, r, p, v, S);
-    apply(p, v, rh);
-    hipLaunchKernelGGL(k_dot_fin<0>, dim3(fin_g), dim3(kRedThreads), 0, st, dpart, dnp, part, S);
-    hipLaunchKernelGGL(k_s<T>, dim3(ew_grid), dim3(256), 0, st, n, r, v, s, S);
-    apply(s, t, s);
-    hipLaunchKernelGGL(k_dot_fin<1>, dim3(fin_g), dim3(kRedThreads), 0, st, dpart, dnp, part, S);
+    const bool fold = dnp > kDirectParts;
+    const double* dp = fold ? dfold : dpart;
+    const int ld = fold ? kFoldParts : dnp;
+    auto dots = [&](const Scal* q) {
+      if (fold)
+        hipLaunchKernelGGL(k_parts, dim3(kFoldParts), dim3(kRedThreads), 0, st, dpart, dnp, dfold,
+                           q);
+    };
+    hipLaunchKernelGGL(k_p<T>, dim3(red_g), dim3(kRedThreads), 0, st, n, r, p, v, S, part, red_g);
+    apply(p, v, rh, S + 1);
+    dots(S + 1);
+    hipLaunchKernelGGL(k_s<T>, dim3(red_g), dim3(kRedThreads), 0, st, n, r, v, s, S, dp, ld, ld);
+    apply(s, t, s, S + 2);
+    dots(S + 2);
     hipLaunchKernelGGL((k_xr<T, TX>), dim3(red_g), dim3(kRedThreads), 0, st, n, x, p, s, t, r, rh,
-                       part, S);
+                       S, dp, ld, ld, part);
     CPM_LAUNCH_CHECK();
   }
 
@@ -475,8 +549,11 @@ struct Bicg {
     CPM_HIP(hipGraphLaunch(gexec, st));
   }
 
-  const Scal& read() {
-    CPM_HIP(hipMemcpyAsync(pin.h, S, sizeof(Scal), hipMemcpyDeviceToHost, st));
+  // The scalars after the iterations so far; force: flag a breakdown.
+  const Scal& read(bool force = false) {
+    hipLaunchKernelGGL(k_settle, dim3(1), dim3(kRedThreads), 0, st, S, part, red_g, force ? 1 : 0);
+    CPM_LAUNCH_CHECK();
+    CPM_HIP(hipMemcpyAsync(pin.h, S + 3, sizeof(Scal), hipMemcpyDeviceToHost, st));
     CPM_HIP(hipStreamSynchronize(st));
     return *pin.h;
   }
@@ -498,9 +575,7 @@ struct Bicg {
       it = h->it;
       if (force_at >= 0 && !forced && !h->done && it >= force_at) {
         forced = true;
-        hipLaunchKernelGGL(k_force_breakdown, dim3(1), dim3(64), 0, st, S);
-        CPM_LAUNCH_CHECK();
-        h = &read();
+        h = &read(true);
       }
       if (h->done && h->breakdown && !(h->rr <= h->tol2)) {
         if (++*restarts > 50) break;
@@ -522,8 +597,9 @@ std::pair<double, double> residual64(const cpm_band* b, hipStream_t st, double m
                                      double* r, double* v, double* part, Scal* S, Pinned& pin) {
   if (tr) apply_transpose_impl<double>(b, m, nn, 1, x, v, st, nullptr, gamma);
   else apply_impl<double>(b, m, nn, 1, x, v, st, nullptr, gamma);
-  hipLaunchKernelGGL(k_res64, dim3(red_grid(b->n)), dim3(kRedThreads), 0, st, b->n, rhs, v, r,
-                     part, S);
+  const int g = red_grid(b->n);
+  hipLaunchKernelGGL(k_res64, dim3(g), dim3(kRedThreads), 0, st, b->n, rhs, v, r, part);
+  hipLaunchKernelGGL(k_res64_fin, dim3(1), dim3(kRedThreads), 0, st, part, g, S);
   CPM_LAUNCH_CHECK();
   CPM_HIP(hipMemcpyAsync(pin.h, S, sizeof(Scal), hipMemcpyDeviceToHost, st));
   CPM_HIP(hipStreamSynchronize(st));
