@@ -65,13 +65,13 @@ def _code(text):
 
 
 def gather_sources_sha1():
-    """Hash of what sets the FP64 tile gather's traffic: its own source (the
-    k_gather templates, the row and cube helpers they call, the Lagrange
-    weights) and the band builder, which fixes the block order and tiles."""
+    """Hash of what sets the FP64 gather's traffic: its own source (k_gather,
+    the row and cube helpers it calls, the Lagrange weights) and the band
+    builder, which fixes the block order and the supertiles."""
     import hashlib
     src = open(os.path.join(ROOT, "paper_2305_04711_amd/csrc/apply.hip")).read()
-    a = src.index("struct TileView {")
-    b = src.index("template <class T>\n__device__ __forceinline__ T wave_sum")
+    a = src.index("// ---------------------------------------------------------------- pass 1")
+    b = src.index("// ---------------------------------------------------------------- pass 2")
     h = hashlib.sha1(_code(src[a:b]).encode())
     for f in ("lagrange.hpp", "builder.hip"):
         h.update(_code(open(os.path.join(ROOT, "paper_2305_04711_amd/csrc", f)).read()).encode())

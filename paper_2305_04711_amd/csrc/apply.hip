@@ -19,19 +19,6 @@
 
 namespace cpm {
 
-struct BlockView {
-  const unsigned long long* mask;
-  const int* off;
-  const int* nbr;
-  const unsigned long long* lrow_mask;
-  const QMeta* face;
-  int nb;
-};
-
-static BlockView bview(const cpm_band* b) {
-  return BlockView{b->blk_mask, b->blk_off, b->blk_nbr, b->lrow_mask, b->blk_face, b->nb};
-}
-
 // Wave-uniform broadcast of lane k (k must be the same in every lane).
 __device__ __forceinline__ int lane_i32(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
 __device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int k) {
@@ -63,51 +50,6 @@ __device__ __forceinline__ unsigned lane_rank(unsigned long long m) {
 __device__ __forceinline__ int xcd_remap(int b, int g) {
   const int q = g >> 3, r = g & 7, x = b & 7, k = b >> 3;
   return x * q + (x < r ? x : r) + k;
-}
-
-struct TileView {
-  const QMeta* meta;
-  const int* tile_blk;
-  const int* tile_start;
-  const int* perm;
-  const double* frac64;
-  const float* frac32;
-  const unsigned* lbase;
-  int ntr;
-  int p;                  // interpolation degree: 3, or 2 (fourth weight 0)
-};
-
-static TileView tview(const cpm_band* b) {
-  return TileView{b->tile_meta, b->tile_blk, b->tile_start, b->perm, b->frac64, b->frac32,
-                  b->lbase, b->n_tile_rows, b->p};
-}
-
-template <int DIM> struct Cube {
-  static constexpr int E = 2 * Geo<DIM>::BX;              // cube edge
-  static constexpr int SIZE = DIM == 3 ? E * E * E : E * E;
-};
-
-// Per-row stencil base (local to the tile block) and fraction.  The fraction
-// is stored in the vector precision TS (FP64 or FP32) and returned in FP64:
-// the weights are always evaluated in FP64, so they sum to one to FP64
-// rounding whatever precision the fraction was stored in.
-template <class TS>
-__device__ __forceinline__ const TS* frac_of(const TileView& tv);
-template <>
-__device__ __forceinline__ const double* frac_of<double>(const TileView& tv) { return tv.frac64; }
-template <>
-__device__ __forceinline__ const float* frac_of<float>(const TileView& tv) { return tv.frac32; }
-
-template <class TS, int DIM>
-__device__ __forceinline__ void row_stencil(const TileView& tv, int pos, int lb[3], double t[3]) {
-  const unsigned p = tv.lbase[pos];
-  const TS* fr = frac_of<TS>(tv);
-  lb[0] = p & 0xff;
-  lb[1] = (p >> 8) & 0xff;
-  lb[2] = DIM == 3 ? (p >> 16) & 0xff : 0;
-#pragma unroll
-  for (int a = 0; a < DIM; ++a) t[a] = (double)fr[(int64_t)a * tv.ntr + pos];
-  if (DIM == 2) t[2] = 0.0;
 }
 
 // ---------------------------------------------------------------- pass 1
@@ -190,13 +132,7 @@ __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lan
 }
 
 // The tile rows of 2 x 2 neighbouring tiles (x and y) are interpolated
-// together.  Their stencils lie in the 3 x 3 x 2 (2-D: 3 x 3) blocks from the
-// corner, of which the last node along each axis is beyond every stencil.
-template <int DIM> struct Super {
-  static constexpr int EX = 3 * Geo<DIM>::BX - 1;              // staged edge, x and y
-  static constexpr int EZ = DIM == 3 ? 2 * Geo<3>::BX - 1 : 1; // staged edge, z
-  static constexpr int NB = DIM == 3 ? 18 : 9;                 // staged blocks
-};
+// together: a supertile (Super), its rows two of a stencil base to a slot.
 struct SuperView {
   const int2* dof;                // [slots] DOFs of a slot's two rows (second -1: one row)
   const unsigned short* base;     // [slots] their stencil base, 4 bits per axis from the corner
@@ -218,6 +154,15 @@ template <> __device__ __forceinline__ double2 frac2_of<double>(const SuperView&
 template <> __device__ __forceinline__ double2 frac2_of<float>(const SuperView& sv, int64_t i) {
   const float2 f = sv.frac32[i];
   return make_double2((double)f.x, (double)f.y);
+}
+
+// fraction of row i (two to a slot) along the axis whose slots begin at s0
+template <class TS> __device__ __forceinline__ double frac_row(const SuperView& sv, int64_t s0, int64_t i);
+template <> __device__ __forceinline__ double frac_row<double>(const SuperView& sv, int64_t s0, int64_t i) {
+  return reinterpret_cast<const double*>(sv.frac64 + s0)[i];
+}
+template <> __device__ __forceinline__ double frac_row<float>(const SuperView& sv, int64_t s0, int64_t i) {
+  return (double)reinterpret_cast<const float*>(sv.frac32 + s0)[i];
 }
 
 // Interpolation of the two rows of a slot from the staged cube (sum-factorised
@@ -263,26 +208,6 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s, const 
   }
 }
 
-// lanes on the low and high face of the block along each axis (slots with
-// local coordinate 0, or BX - 1, along it), evaluated at compile time
-template <int DIM>
-struct FaceLanes {
-  unsigned long long lo[3], hi[3];
-};
-template <int DIM>
-constexpr FaceLanes<DIM> face_lanes() {
-  FaceLanes<DIM> f{{0ull, 0ull, 0ull}, {0ull, 0ull, 0ull}};
-  constexpr int BX = DIM == 3 ? 4 : 8;
-  for (int d = 0; d < DIM; ++d)
-    for (int s = 0; s < 64; ++s) {
-      const int l = DIM == 3 ? (d == 0 ? s & 3 : d == 1 ? (s >> 2) & 3 : s >> 4)
-                             : (d == 0 ? s & 7 : s >> 3);
-      if (l == 0) f.lo[d] |= 1ull << s;
-      if (l == BX - 1) f.hi[d] |= 1ull << s;
-    }
-  return f;
-}
-
 // Pass 1 in one launch of single wavefronts: the first er.groups take
 // explicit rows, the others a supertile each (er.groups is a multiple of 8,
 // so both parts keep the XCD of a workgroup id).
@@ -308,7 +233,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   using G = Geo<DIM>;
   using SP = Super<DIM>;
   constexpr int EX = SP::EX, EP = EX + PAD, BX = G::BX, NB = SP::NB;
-  constexpr FaceLanes<DIM> FL = face_lanes<DIM>();
+  constexpr InsideMasks<DIM> IN = inside_masks<DIM>();
   constexpr int CS = SP::EZ * EX * EP;
   __shared__ double s_u[CS + 1];
   const int lane = threadIdx.x;
@@ -357,10 +282,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
-      unsigned long long in = ~0ull;
-      if (qx == 2) in &= ~FL.hi[0];
-      if (qy == 2) in &= ~FL.hi[1];
-      if (DIM == 3 && qz == 1) in &= ~FL.hi[DIM - 1];
+      const unsigned long long in = IN.m[q];
       const int off = (DIM == 3 ? (qz * BX * EX + qy * BX) * EP : qy * BX * EP) + qx * BX;
       s_u[in == ~0ull || lane_in(in) ? cell0 + off : CS] = (double)x[q];
     }
@@ -379,12 +301,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       }
     }
   }
-}
-
-template <class T>
-__device__ __forceinline__ T wave_sum(T v, int width) {
-  for (int o = width >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, width);
-  return v;
 }
 
 // Workgroup sums of d0 and d1 (256 threads, every one must call it), written
@@ -460,6 +376,26 @@ template <int K> constexpr int dpp_shr() { return 0x110 + K; }   // from lane - 
 template <int K> constexpr int dpp_shl() { return 0x100 + K; }   // from lane + K
 
 
+// lanes on the low and high face of the block along each axis (slots with
+// local coordinate 0, or BX - 1, along it), evaluated at compile time
+template <int DIM>
+struct FaceLanes {
+  unsigned long long lo[3], hi[3];
+};
+template <int DIM>
+constexpr FaceLanes<DIM> face_lanes() {
+  FaceLanes<DIM> f{{0ull, 0ull, 0ull}, {0ull, 0ull, 0ull}};
+  constexpr int BX = DIM == 3 ? 4 : 8;
+  for (int d = 0; d < DIM; ++d)
+    for (int s = 0; s < 64; ++s) {
+      const int l = DIM == 3 ? (d == 0 ? s & 3 : d == 1 ? (s >> 2) & 3 : s >> 4)
+                             : (d == 0 ? s & 7 : s >> 3);
+      if (l == 0) f.lo[d] |= 1ull << s;
+      if (l == BX - 1) f.hi[d] |= 1ull << s;
+    }
+  return f;
+}
+
 // Explicit FD rows (swapped PDE rows and BC rows), one thread each.
 struct LRows {
   int n, groups;          // rows; workgroups that hold them
@@ -468,6 +404,30 @@ struct LRows {
   const int* col;
   const int* inst;        // composite: instance of each row
 };
+
+// The transpose's explicit FD rows by pull lists: target k of the ascending
+// list takes +-co w of the rows src[start[k] .. start[k + 1]) (an entry is
+// 2 row + (1: subtracted)), in that order.  blk and bc find the targets of a
+// block and of a BC DOF.
+struct LPull {
+  const Pull* blk;
+  const int* bc;
+  const int* start;
+  const int* src;
+  const int* row_id;
+  int n_s, n_c;
+};
+template <class TU>
+__device__ __forceinline__ double pull_rows(const LPull& lp, int64_t k, const TU* __restrict__ w,
+                                            double co) {
+  double acc = 0.0;
+  for (int e = lp.start[k], e1 = lp.start[k + 1]; e < e1; ++e) {
+    const int v = lp.src[e];
+    const double wi = co * (double)w[lp.row_id[v >> 1]];
+    acc += (v & 1) ? -wi : wi;
+  }
+  return acc;
+}
 
 // Fused dot products of the pass: with y set, the partials of (y, v) and
 // (v, v) of right-hand side r go to part + 2 r np, one per workgroup.
@@ -482,10 +442,11 @@ struct DotOut {
 constexpr int kLapBlocksPerWave = 2;
 constexpr int kLapBlocksPerGroup = 4 * kLapBlocksPerWave;
 
-// The first lr.groups workgroups take explicit rows, the others blocks.
+// The first lr.groups workgroups take explicit rows (ALL: the BC entries), the
+// others blocks.
 template <class TU, class TA, class TV, int DIM, bool ALL, bool DOT = false>
 __global__ __launch_bounds__(256) void k_lap(
-    LRows lr, const QMeta* __restrict__ face, int nb, const TU* __restrict__ u,
+    LRows lr, LPull lp, const QMeta* __restrict__ face, int nb, const TU* __restrict__ u,
     const TA* __restrict__ a, TV* __restrict__ v, int64_t ld, int nrhs, double cd, double co,
     const double* __restrict__ gsum, double gscale, int xcd, const double* __restrict__ coef,
     Skip skip, DotOut<TV> dot) {
@@ -493,6 +454,15 @@ __global__ __launch_bounds__(256) void k_lap(
   constexpr int BX = G::BX, KB = kLapBlocksPerWave;
   constexpr int step[3] = {1, BX, BX * BX};
   constexpr FaceLanes<DIM> FL = face_lanes<DIM>();
+  if (ALL && (int)blockIdx.x < lr.groups) {   // BC entries: explicit rows only
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= lp.n_c) return;
+    const int k = lp.bc[i];
+    for (int r = 0; r < nrhs; ++r)
+      if (!skipped(skip, r, 0))
+        v[r * ld + lp.n_s + i] = (TV)(k >= 0 ? pull_rows(lp, k, u + r * ld, co) : 0.0);
+    return;
+  }
   if (!ALL && (int)blockIdx.x < lr.groups) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int id = i < lr.n ? lr.id[i] : -1;
@@ -539,8 +509,12 @@ __global__ __launch_bounds__(256) void k_lap(
   int own[KB], xdof[KB][DIM], inst = 0;
   // entry e of block j's metadata in lane 8 j + e: one load, no chain of
   // scalar ones
-  const int4 fm = reinterpret_cast<const int4*>(
-      face)[(int64_t)min(blk0 + min(lane >> 3, KB - 1), nb - 1) * 8 + (lane & 7)];
+  // (ALL: and its explicit targets in lane 8 KB + j)
+  const int4* fp = reinterpret_cast<const int4*>(face) +
+                   ((int64_t)min(blk0 + min(lane >> 3, KB - 1), nb - 1) * 8 + (lane & 7));
+  if (ALL && lane >= 8 * KB)
+    fp = reinterpret_cast<const int4*>(lp.blk) + min(blk0 + min(lane - 8 * KB, KB - 1), nb - 1);
+  const int4 fm = *fp;
   auto fmask = [&](int j, int e) {
     return ((unsigned long long)(unsigned)lane_i32(fm.y, 8 * j + e) << 32) |
            (unsigned)lane_i32(fm.x, 8 * j + e);
@@ -633,6 +607,14 @@ __global__ __launch_bounds__(256) void k_lap(
       }
       if (lane_in(outm[j])) {
         double o = ALL ? coi[j] * sum : lap_out(cdi[j], uv[j], coi[j], sum);
+        if constexpr (ALL) {
+          const unsigned long long t =
+              ((unsigned long long)(unsigned)lane_i32(fm.y, 8 * KB + j) << 32) |
+              (unsigned)lane_i32(fm.x, 8 * KB + j);
+          if (lane_in(t))
+            o += pull_rows(lp, lane_i32(fm.z, 8 * KB + j) + (int64_t)lane_rank(t), u + r * ld,
+                           coi[j]);
+        }
         if (gsum) o += gscale * gsum[r];
         const TV ov = (TV)o;
         v[r * ld + own[j]] = ov;
@@ -683,251 +665,337 @@ __global__ void k_sum_final(const double* part, int np, double* out) {
 }
 
 // ---------------------------------------------------------------- transpose
-// E^T c for the tile rows of one parity class, one wavefront per tile.  The
-// wave takes its tile and row range from one entry of the class table, so the
-// tile's metadata and first row data are requested together, one load after
-// it.  Rows go in chunks of kTRows: each lane of a chunk puts the stencil
-// base of one row into LDS with the row's 1-D weights (the forward gather's
-// FP64 weights), c_i folded into the last factor; then the wave walks the
-// chunk's rows with one lane per stencil member (4 rows at a time in 2-D,
-// where a stencil has 16 members), adding w c_i into the tile's (2 BX)^d cube
-// in LDS.  A 3-D member's weight is the product of three 1-D weights read
-// from LDS, and each lane sums over runs of rows with the same stencil base;
-// 2-D uses LDS atomic adds (rows past the last one carry zero weights).  The
-// cube is accumulated in FP64 for both precisions.  It is then added into z
-// with plain loads and stores: tiles of one parity class stage disjoint
-// blocks and the classes run as successive launches, so no two waves of a
-// launch touch the same entry of z.  Chunks of 32 rows keep the LDS of a wave
-// at 7.9 KB (20 waves per CU) where whole 64-row passes took 11.1 KB (14).
-constexpr int kTRows = 32;
-constexpr int kTGroup = 4;
-template <class TS, int DIM>
-__global__ __launch_bounds__(64) void k_gather_T(BlockView B, TileView tv, const int4* __restrict__ tbl,
-                                                 int N, const double* __restrict__ c,
-                                                 double* __restrict__ z, int64_t ld, int r,
-                                                 int xcd) {
+// E^T c over the explicit rows by pull lists: entry e of the list has weight
+// w[e] and source row src[e]; target k's entries are start[k] .. start[k + 1).
+struct EPull {
+  int n, groups;          // targets; wavefronts that hold them (a multiple of 8)
+  const int* start;
+  const int* src;
+  const double* w;
+};
+constexpr int kEPullTargets = 4;   // targets per wavefront whose loads go out together
+
+// x[k] = sum of target k's products w c_src: the lanes take the entries 64 at
+// a time and sum their own in order, then the lanes' sums in a fixed order.
+__device__ __forceinline__ void explicit_targets(const EPull& ep, int wave, int lane,
+                                                 const double* __restrict__ c,
+                                                 double* __restrict__ x) {
+  int b0[kEPullTargets], b1[kEPullTargets], longest = 0;
+#pragma unroll
+  for (int j = 0; j < kEPullTargets; ++j) {
+    const int k = min(wave * kEPullTargets + j, ep.n - 1);
+    b0[j] = ep.start[k];
+    b1[j] = ep.start[k + 1];
+    longest = max(longest, b1[j] - b0[j]);
+  }
+  double acc[kEPullTargets] = {0.0, 0.0, 0.0, 0.0};
+  for (int o = lane; o - lane < longest; o += 64) {
+    int src[kEPullTargets];
+    double w[kEPullTargets], v[kEPullTargets];
+#pragma unroll
+    for (int j = 0; j < kEPullTargets; ++j) {
+      const int e = min(b0[j] + o, b1[j] - 1);   // every target has an entry
+      src[j] = ep.src[e];
+      w[j] = ep.w[e];
+    }
+#pragma unroll
+    for (int j = 0; j < kEPullTargets; ++j) v[j] = c[src[j]];
+#pragma unroll
+    for (int j = 0; j < kEPullTargets; ++j)
+      acc[j] += b0[j] + o < b1[j] ? w[j] * v[j] : 0.0;
+  }
+#pragma unroll
+  for (int j = 0; j < kEPullTargets; ++j) {
+    const double s = lanes_sum<64>(acc[j]);
+    if (lane == 63 && wave * kEPullTargets + j < ep.n) x[wave * kEPullTargets + j] = s;
+  }
+}
+
+// Orders a wavefront's LDS accesses among its lanes: the hardware takes them in
+// program order, so only the compiler is held back.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// E^T c of the tile rows, a workgroup of W wavefronts per supertile.  The rows
+// of one stencil base add w c into the same 4^d members, a small matrix
+// product summed over the rows: in 3-D G[z][y][x] += sum_i (c_i wz_i[z]
+// wy_i[y]) wx_i[x], four 4 x 4 blocks (z) with four rows to an instruction of
+// the FP64 matrix unit, whose accumulator is one register (a member) per lane;
+// in 2-D one 4 x 4 block, with sixteen rows in the four places, added up at
+// the end.  Slots go in chunks of kTSlots: each lane puts a row's 1-D weights
+// into LDS (c_i folded into the last), then the wave walks the chunk in steps
+// of up to four (2-D: sixteen) rows of one base, kTSteps steps' reads at once,
+// and adds each step's members into its cube in LDS without reading it back
+// (a step's members are distinct cells and a wave's LDS operations complete in
+// order, so the sum's order is fixed).  The cube's entries of the blocks'
+// nodes, summed over the waves in order, then go to the supertile's part of
+// buf, one after the other, where k_combine finds them (Pull): no order
+// between supertiles, no clearing, one launch.  The explicit targets come last
+// and fill the chip while the last supertiles end (torus at h = 1/256: 414 to
+// 403 us for the whole transpose).
+//
+// What bounds it: LDS (55% of the cycles: three reads and one add a step) and
+// the vector unit (41%) at 11 waves per CU at large sizes, a wave's chain of
+// steps at small ones.  Whole transposes, FP64: torus at h = 1/256 (8.6M DOFs)
+// 647 us with lane = member, one row at a time and a launch per parity class,
+// 453 with one step at a time whose sums are read, added and written back,
+// 403 now; sphere at h = 1/48, FP32, two right-hand sides: 319, 76 and 53.
+// Chunks of 16, 32 slots: 432, 414 us; 4, 8 steps at once: 414, 434.
+constexpr int kTSlots = 32, kTSteps = 4;
+// Two waves share a supertile where there are few: they halve its chain, but
+// fill and clear two cubes.  One wave, two: 28.6, 21.8 us at 0.1M DOFs (600
+// supertiles); 45.6, 41.7 at 2300; 60.6, 60.6 at 4500; 100, 109 at 9100.
+constexpr int kTSplitBelow = 4096;
+template <class TS, int DIM, int W>
+__global__ __launch_bounds__(64 * W) void k_gather_T(EPull ep, SuperView sv,
+                                                     const QMeta* __restrict__ meta,
+                                                     const int4* __restrict__ rng,
+                                                     const double* __restrict__ c,
+                                                     double* __restrict__ x,
+                                                     double* __restrict__ buf, int64_t ld,
+                                                     int64_t bufld, int r0, int xcd, Skip skip) {
   using G = Geo<DIM>;
-  constexpr int E = Cube<DIM>::E, EP = E + 1, NQ = 1 << DIM;
-  constexpr int CS = DIM == 3 ? E * E * EP : E * EP;
-  constexpr int M = DIM == 3 ? 64 : 16;       // stencil members
-  constexpr int RPI = 64 / M;                 // rows per wave instruction
+  using SP = Super<DIM>;
+  constexpr int EX = SP::EX, EP = EX + 1, BX = G::BX, NB = SP::NB;
   constexpr int NW = DIM == 3 ? 12 : 8;       // 1-D weights per row
-  constexpr int RC = kTRows;
-  constexpr int RG = kTGroup;                 // rows whose LDS reads go out together
-  static_assert(RC % 16 == 0 && RC <= 64 && RC % RG == 0, "chunk rows: a multiple of 16 and RG");
-  __shared__ double s_z[CS];
-  // per-row 1-D weights, component major; rows padded to RC + 1 entries so
-  // that the four values of one component a wave reads for a row lie in
-  // distinct LDS banks
-  __shared__ double s_w[NW][RC + 1];
-  __shared__ int s_b[RC];                     // per-row cube offset of member 0
-  const int4 te = tbl[xcd ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x];
-  const int t = te.x, beg = te.y, end = te.z;
-  if (beg == end) return;
-  const int lane = threadIdx.x;
-  unsigned long long qm = 0ull;
-  int qoff = 0;
-  if (lane < NQ) {
-    const QMeta q = tv.meta[(int64_t)t * 8 + lane];
-    qm = q.mask;
-    qoff = q.off;
+  constexpr int RC = 2 * kTSlots;             // rows of a chunk
+  constexpr int RS = DIM == 3 ? 4 : 16;       // rows of a matrix instruction
+  // Strides at which a half-wave's cells, and a step's weights, lie in
+  // distinct banks.
+  constexpr int PL = DIM == 3 ? 136 : EX * EP, CS = SP::EZ * PL;
+  constexpr int WS = RC + RS;
+  constexpr int U = kTSteps;
+  constexpr InsideMasks<DIM> IN = inside_masks<DIM>();
+  static_assert(RC <= 64, "a row per lane");
+  static_assert(PL >= EX * EP, "planes apart");
+  __shared__ double s_z[W][CS + 1];
+  __shared__ double s_w[W][NW * WS];
+  const int lane = threadIdx.x & 63;
+  const int wv = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = blockIdx.y;
+  if (skipped(skip, r0 + r, 0)) return;
+  c += (r0 + r) * ld;
+  int g = blockIdx.x;
+  if (g >= sv.n) {
+    g -= sv.n;
+    if (xcd) g = xcd_remap(g, ep.groups / W);
+    g = g * W + wv;
+    if (g * kEPullTargets < ep.n) explicit_targets(ep, g, lane, c, x + (int64_t)r * ep.n);
+    return;
   }
-  // entry of z (or -1) of this lane's node in staged block q, and its cube cell
-  const int cx0 = G::lx(lane), cy0 = G::ly(lane), cz0 = G::lz(lane);
-  auto zidx = [&](int q) {
-    const unsigned long long m = lane_u64(qm, q);
-    const int off = lane_i32(qoff, q);
-    return ((m >> lane) & 1ull) ? off + __popcll(m & ((1ull << lane) - 1ull)) : -1;
+  if (xcd) g = xcd_remap(g, sv.n);
+  const int4 rg = rng[g];
+  const int4 qm = reinterpret_cast<const int4*>(meta)[(int64_t)g * NB + min(lane, NB - 1)];
+  const int* dofs = reinterpret_cast<const int*>(sv.dof);
+  // row data of the lane's row of a chunk (its last row's past the end: loads
+  // under no branch); the wave's next chunk's is requested before a chunk is
+  // walked, the DOFs (which c is read through) one chunk further ahead
+  const int rows = 2 * rg.y;
+  const int64_t first = 2 * (int64_t)rg.x;
+  auto at = [&](int k) { return first + min(k + (lane & (RC - 1)), rows - 1); };
+  auto frac = [&](int k, double t[DIM]) {
+    const int64_t i = at(k);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) t[d] = frac_row<TS>(sv, d * sv.ns, i);
   };
-  auto cell = [&](int q) {
-    const int qx = q & 1, qy = (q >> 1) & 1, qz = DIM == 3 ? (q >> 2) : 0;
-    const int cx = qx * G::BX + cx0, cy = qy * G::BX + cy0, cz = qz * G::BX + cz0;
-    return DIM == 3 ? (cz * E + cy) * EP + cx : cy * EP + cx;
-  };
-  // the old entries of z under the staged blocks, requested now so that the
-  // loads overlap the row work (no other wave of this launch touches them);
-  // the cube starts at zero and is added to them at the end
-  double old[NQ];
+  double t[DIM], ci;
+  const int kw = wv * RC;
+  int code, dof = dofs[at(kw)], dofn = dofs[at(kw + W * RC)];
+  frac(kw, t);
+  code = sv.base[at(kw) >> 1];
+  ci = c[max(dof, 0)];
+  double* z = s_z[wv];
+  double* ws = s_w[wv];
+  for (int k = lane; k < CS + 1; k += 64) z[k] = 0.0;
+  for (int k = lane; k < NW * RS; k += 64) ws[(k / RS) * WS + RC + k % RS] = 0.0;
+  // the lane's operands: rows rk of a step, entries ia (A) and ja (B), and its
+  // member's cell
+  const int rk = DIM == 3 ? lane >> 4 : (lane >> 4) + 4 * ((lane >> 2) & 3);
+  const int ia = lane & 3, iz = (lane >> 2) & 3;
+  double* cell = z + (DIM == 3 ? iz * PL : 0) + (lane >> 4) * EP + (lane & 3);
+  const double* wb = ws + ia * WS + rk;
+  const double* wz = ws + (8 + iz) * WS + rk;
+  for (int k0 = kw; k0 < rows; k0 += W * RC) {
+    const int nr = min(RC, rows - k0);                // rows of this chunk
+    double w[DIM][4];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int zi = zidx(q);
-    old[q] = zi >= 0 ? z[r * ld + zi] : 0.0;
-  }
-  for (int idx = lane; idx < CS; idx += 64) s_z[idx] = 0.0;
-  // this lane's stencil member and row slot within an instruction
-  const int mo = lane & (M - 1), sub = lane / M;
-  const int ma = mo & 3, mb = (mo >> 2) & 3, mc = DIM == 3 ? (mo >> 4) : 0;
-  const int moff = DIM == 3 ? (mc * E + mb) * EP + ma : mb * EP + ma;
-  // Row data of a chunk (lane < RC: row p0 + lane): local base, fraction
-  // and c.  The next chunk's is requested before the current chunk's rows
-  // are walked, and the DOFs (which c is read through) one chunk further
-  // ahead, so only the first chunk waits for its loads.
-  int lbn[3] = {0, 0, 0}, pmn = 0;
-  double ttn[3] = {0.0, 0.0, 0.0}, cn = 0.0;
-  if (lane < RC && beg + lane < end) {
-    row_stencil<TS, DIM>(tv, beg + lane, lbn, ttn);
-    cn = c[r * ld + tv.perm[beg + lane]];
-  }
-  if (lane < RC && beg + RC + lane < end) pmn = tv.perm[beg + RC + lane];
-  for (int p0 = beg; p0 < end; p0 += RC) {
-    const int nrow = min(RC, end - p0);
-    const int lb[3] = {lbn[0], lbn[1], lbn[2]};
-    const double tt[3] = {ttn[0], ttn[1], ttn[2]}, ci = cn;
-    const int p1 = p0 + RC;
-    if (lane < RC && p1 + lane < end) {
-      row_stencil<TS, DIM>(tv, p1 + lane, lbn, ttn);
-      cn = c[r * ld + pmn];
-    }
-    if (lane < RC && p1 + RC + lane < end) pmn = tv.perm[p1 + RC + lane];
-    double wx[4] = {0.0, 0.0, 0.0, 0.0}, wy[4] = {0.0, 0.0, 0.0, 0.0};
-    double wz[4] = {0.0, 0.0, 0.0, 0.0};
-    int bs = 0;
-    if (lane < nrow) {
-      lagrange_p<double>(tv.p, tt[0], wx);
-      lagrange_p<double>(tv.p, tt[1], wy);
-      if (DIM == 3) {
-        lagrange_p<double>(tv.p, tt[2], wz);
+    for (int d = 0; d < DIM; ++d) lagrange_p<double>(sv.p, t[d], w[d]);
+    const double cw = dof >= 0 ? ci : 0.0;            // a lone row's partner adds nothing
 #pragma unroll
-        for (int k = 0; k < 4; ++k) wz[k] *= ci;
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) wy[k] *= ci;
-      }
-      bs = DIM == 3 ? (lb[2] * E + lb[1]) * EP + lb[0] : lb[1] * EP + lb[0];
-    }
+    for (int o = 0; o < 4; ++o) w[DIM - 1][o] *= cw;
+    const int codes = code;
+    // requested ahead
+    frac(k0 + W * RC, t);
+    code = sv.base[at(k0 + W * RC) >> 1];
+    dof = dofn;
+    ci = c[max(dofn, 0)];
+    dofn = dofs[at(k0 + 2 * W * RC)];
+    wave_sync();   // the previous chunk is walked
     if (lane < RC) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        s_w[k][lane] = wx[k];
-        s_w[4 + k][lane] = wy[k];
-        if constexpr (DIM == 3) s_w[8 + k][lane] = wz[k];
-      }
-      s_b[lane] = bs;
+      for (int d = 0; d < DIM; ++d)
+#pragma unroll
+        for (int o = 0; o < 4; ++o) ws[(4 * d + o) * WS + lane] = w[d][o];
     }
-    __syncthreads();
-    if constexpr (DIM == 3) {
-      // Rows are sorted by stencil base, and runs of rows share one: each
-      // lane sums its member's contributions in a register while the base
-      // stays the same and adds the sum into the cube when it changes.  A
-      // row's 64 members are distinct cells, and a wave's LDS operations
-      // complete in order, so these read-add-writes need no atomics.
-      double acc = 0.0;
-      int cur = __builtin_amdgcn_readfirstlane(s_b[0]);
-      for (int j = 0; j < nrow; j += RG) {
-        // RG rows' bases and weights read at once (indices stay below RC)
-        int bq[RG];
-        double wq[RG];
+    wave_sync();
+    // A step is up to RS rows of one base: the rows at which a base begins,
+    // the row's place in its base's, and the rows at which a step begins.
+    const unsigned long long starts =
+        __ballot(codes != __builtin_amdgcn_update_dpp(-1, codes, 0x138, 0xf, 0xf, false));
+    const int place = lane - (63 - __clzll((long long)(starts & (~0ull >> (63 - lane)))));
+    unsigned long long steps = __ballot(place % RS == 0 && lane < nr);
+    const int off = ((DIM == 3 ? (codes >> 8) * PL : 0) + ((codes >> 4) & 15) * EP + (codes & 15)) * 8;
+    while (steps) {
+      // U steps at a time, the reads of all first; past the last: no rows
+      int k[U], m[U], o[U];
 #pragma unroll
-        for (int u = 0; u < RG; ++u) {
-          bq[u] = __builtin_amdgcn_readfirstlane(s_b[j + u]);
-          wq[u] = (s_w[ma][j + u] * s_w[4 + mb][j + u]) * s_w[8 + mc][j + u];
-        }
-#pragma unroll
-        for (int u = 0; u < RG; ++u) {
-          if (j + u >= nrow) break;
-          if (bq[u] != cur) {
-            s_z[cur + moff] += acc;
-            acc = 0.0;
-            cur = bq[u];
-          }
-          acc += wq[u];
-        }
+      for (int j = 0; j < U; ++j) {
+        k[j] = steps ? __ffsll((long long)steps) - 1 : 0;
+        const unsigned long long rest = steps & (steps - 1);
+        m[j] = steps ? (rest ? __ffsll((long long)rest) - 1 : nr) - k[j] : 0;
+        o[j] = lane_i32(off, k[j]);
+        steps = steps ? rest : 0;
       }
-      s_z[cur + moff] += acc;
-    } else {
-      constexpr int UR = 4;                   // rows per lane per step
-      const int nr = (nrow + UR * RPI - 1) / (UR * RPI) * (UR * RPI);
-      for (int j0 = 0; j0 < nr; j0 += UR * RPI) {
-        double v[UR];
-        int o[UR];
+      double A0[U], A1[U], B[U], acc[U];
 #pragma unroll
-        for (int u = 0; u < UR; ++u) {
-          const int j = j0 + u * RPI + sub;
-          v[u] = s_w[ma][j] * s_w[4 + mb][j];
-          o[u] = s_b[j] + moff;
+      for (int j = 0; j < U; ++j) {
+        A0[j] = (wb + 4 * WS)[k[j]];
+        if (DIM == 3) A1[j] = wz[k[j]];
+        B[j] = wb[k[j]];
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        double A = DIM == 3 ? A0[j] * A1[j] : A0[j];
+        A = rk < m[j] ? A : 0.0;
+        acc[j] = __builtin_amdgcn_mfma_f64_4x4x4f64(A, B[j], 0.0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        if constexpr (DIM == 2) {
+          // the four places' sums of the lanes 4 and 8 apart
+          acc[j] = dpp_add<0x124>(acc[j]);
+          acc[j] = dpp_add<0x128>(acc[j]);
         }
-#pragma unroll
-        for (int u = 0; u < UR; ++u) atomicAdd(&s_z[o[u]], v[u]);
+        double* to = reinterpret_cast<double*>(reinterpret_cast<char*>(cell) + o[j]);
+        if (DIM == 3 || iz == 0)
+          (void)__hip_atomic_fetch_add(to, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
-    __syncthreads();
+  }
+  if (W > 1) __syncthreads();
+  else wave_sync();
+  // the cube's entries of the staged blocks' nodes, summed over the waves
+  double* out = buf + (int64_t)r * bufld + (int64_t)g * SP::CELLS;
+  const int cell0 = DIM == 3 ? G::lz(lane) * PL + G::ly(lane) * EP + G::lx(lane)
+                             : G::ly(lane) * EP + G::lx(lane);
+  double v[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
+    const unsigned long long in = IN.m[q];
+    const int off = (DIM == 3 ? qz * BX * PL : 0) + qy * BX * EP + qx * BX;
+    const int at_q = in == ~0ull || lane_in(in) ? cell0 + off : CS;
+    if (W > 1 && q % W != wv) continue;
+    v[q] = s_z[0][at_q];
+#pragma unroll
+    for (int j = 1; j < W; ++j) v[q] += s_z[j][at_q];
   }
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int zi = zidx(q);
-    if (zi >= 0) z[r * ld + zi] = old[q] + s_z[cell(q)];
-  }
-}
-
-// E^T c over the explicit rows by pull lists: one wavefront per target DOF
-// (four per workgroup).  The lanes take the target's contiguous segment of
-// entries 64 at a time (entry e: weight w[e] of source row src[e], FP64 for
-// both precisions), sum the products w c_src in their own order and the wave
-// adds the tree sum of its lanes into z once: the same value on every run,
-// with no atomics.
-__global__ __launch_bounds__(256) void k_et_pull(int n_tgt, const int* __restrict__ tgt,
-                                                 const int* __restrict__ start,
-                                                 const int* __restrict__ src,
-                                                 const double* __restrict__ w,
-                                                 const double* __restrict__ c,
-                                                 double* __restrict__ z) {
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (k >= n_tgt) return;                     // whole waves leave together
-  const int lane = threadIdx.x & 63;
-  const int b0 = start[k], b1 = start[k + 1];
-  double acc = 0.0;
-  for (int e = b0 + lane; e < b1; e += 64) acc += w[e] * c[src[e]];
-  acc = wave_sum(acc, 64);
-  if (lane == 0) z[tgt[k]] += acc;
-}
-
-// The corrections of (L - diag L)^T w for explicit FD rows by pull lists:
-// c[t] += co (sum of +w_i over rows adding to t, -w_i over swapped rows
-// moving their entry away from t), in ascending source order.
-template <class TS>
-__global__ void k_lt_pull(int n_tgt, const int* __restrict__ tgt, const int* __restrict__ start,
-                          const int* __restrict__ src, const int* __restrict__ row_id,
-                          const TS* __restrict__ w, double* __restrict__ c, int64_t ld, int nrhs,
-                          double co) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_tgt) return;
-  const int t = tgt[k], b0 = start[k], b1 = start[k + 1];
-  for (int r = 0; r < nrhs; ++r) {
-    double acc = 0.0;
-    for (int e = b0; e < b1; ++e) {
-      const int v = src[e];
-      const double wi = co * (double)w[r * ld + row_id[v >> 1]];
-      acc += (v & 1) ? -wi : wi;
-    }
-    c[r * ld + t] += acc;
+  for (int q = 0; q < NB; ++q) {
+    const unsigned long long m = IN.m[q] & (((unsigned long long)(unsigned)lane_i32(qm.y, q) << 32) |
+                                            (unsigned)lane_i32(qm.x, q));
+    if ((W == 1 || q % W == wv) && lane_in(m)) out[lane_count_below(m, 0)] = v[q];
+    out += __popcll(m);
   }
 }
 
-template <class T>
-__global__ void k_fill(T* __restrict__ p, int64_t n, T val) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = val;
-}
-
-// out = cd w + nn e (FP64 arithmetic, stored in the vector precision TS);
-// with DOT also the partials of (dy, out) and (out, out)
-template <class TS, bool DOT = false>
-__global__ void k_combine(const TS* __restrict__ w, const double* __restrict__ z,
-                          TS* __restrict__ out, double cd, double nn, int64_t total,
-                          const TS* __restrict__ dy = nullptr, double* __restrict__ dpart = nullptr,
-                          int dnp = 0) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// z = cd w + nn E^T c, with E^T c of a node the sum of what its block's
+// supertiles and its explicit rows stored (Pull, in the entries' order); lane
+// = slot of a block, two blocks per wavefront.  The first bc.groups workgroups
+// take the BC entries, which only explicit rows reach.  With DOT also the
+// partials of (dy, z) and (z, z), one per workgroup.
+struct BcPull {
+  const int* et;          // [n_c] explicit target of a BC DOF, or -1
+  int groups, n_s, n_c;
+};
+template <class TS, int DIM, bool DOT>
+__global__ __launch_bounds__(256) void k_combine(BcPull bc, const QMeta* __restrict__ face,
+                                                 const Pull* __restrict__ pull, int nb,
+                                                 const double* __restrict__ buf,
+                                                 const double* __restrict__ x, int64_t bufld,
+                                                 int n_et, const TS* __restrict__ w,
+                                                 TS* __restrict__ z, int64_t ld, int r0, double cd,
+                                                 double nn, int xcd, DotOut<TS> dot, Skip skip) {
+  constexpr int KB = kLapBlocksPerWave, NP = 1 << DIM;
+  const int r = blockIdx.y;
+  if (skipped(skip, r0 + r, 0)) return;
+  w += (r0 + r) * ld;
+  z += (r0 + r) * ld;
+  buf += (int64_t)r * bufld;
+  x += (int64_t)r * n_et;
   double d0 = 0.0, d1 = 0.0;
-  if (i < total) {
-    const TS o = (TS)(cd * (double)w[i] + nn * z[i]);
-    out[i] = o;
+  int part = blockIdx.x;
+  auto put = [&](int i, double wv, double e, double y) {
+    const TS o = (TS)(cd * wv + nn * e);
+    z[i] = o;
     if (DOT) {
-      d0 = (double)dy[i] * (double)o;
-      d1 = (double)o * (double)o;
+      d0 += y * (double)o;
+      d1 += (double)o * (double)o;
+    }
+  };
+  if ((int)blockIdx.x < bc.groups) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < bc.n_c) {
+      const int k = bc.et[i];
+      put(bc.n_s + i, (double)w[bc.n_s + i], k >= 0 ? x[k] : 0.0,
+          DOT ? (double)dot.y[bc.n_s + i] : 0.0);
+    }
+  } else {
+    const int ng = gridDim.x - bc.groups, gb = blockIdx.x - bc.groups;
+    const int wg = xcd ? xcd_remap(gb, ng) : gb;
+    part = bc.groups + wg;
+    const int blk0 = (wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * KB;
+    const int lane = threadIdx.x & 63;
+    // entry e of block j in lane 16 j + e: its supertiles' and explicit
+    // targets' (0 .. NP - 1, 8), and the block's own mask and first DOF (15)
+    const int jb = min(blk0 + min(lane >> 4, KB - 1), nb - 1), e = lane & 15;
+    const int4 pm = e == 15 ? reinterpret_cast<const int4*>(face)[(int64_t)jb * 8]
+                            : reinterpret_cast<const int4*>(pull)[(int64_t)jb * 9 + min(e, 8)];
+    auto mask = [&](int j, int q) {
+      return ((unsigned long long)(unsigned)lane_i32(pm.y, 16 * j + q) << 32) |
+             (unsigned)lane_i32(pm.x, 16 * j + q);
+    };
+    auto from = [&](int j, int q) {
+      return ((long long)lane_i32(pm.w, 16 * j + q) << 32) | (unsigned)lane_i32(pm.z, 16 * j + q);
+    };
+    double s[KB][NP + 1];
+    TS wl[KB], yl[KB];
+    int own[KB];
+    // every load first (a lane without an entry loads its block's first)
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      own[j] = lane_i32(pm.z, 16 * j + 15) + (int)lane_rank(mask(j, 15));
+      wl[j] = w[own[j]];
+      if (DOT) yl[j] = dot.y[own[j]];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) s[j][q] = (buf + from(j, q))[lane_rank(mask(j, q))];
+      s[j][NP] = mask(j, 8) ? (x + from(j, 8))[lane_rank(mask(j, 8))] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      double ev = 0.0;
+#pragma unroll
+      for (int q = 0; q <= NP; ++q) {
+        asm volatile("" : "+v"(s[j][q]));   // the loads stay above
+        ev += lane_in(mask(j, q < NP ? q : 8)) ? s[j][q] : 0.0;
+      }
+      if (blk0 + j < nb && lane_in(mask(j, 15)))
+        put(own[j], (double)wl[j], ev, DOT ? (double)yl[j] : 0.0);
     }
   }
-  if constexpr (DOT) group_dot2(d0, d1, dpart, dnp, blockIdx.x);
+  if constexpr (DOT) group_dot2(d0, d1, dot.part, dot.np, part);
 }
 
 // ---------------------------------------------------------------- rhs
@@ -1038,11 +1106,12 @@ static int lap_groups(const cpm_band* b) {
   return (b->nb + kLapBlocksPerGroup - 1) / kLapBlocksPerGroup;
 }
 static int lap_row_groups(const cpm_band* b) { return (b->n_lrows + 255) / 256; }
+static int bc_groups(const cpm_band* b) { return (int)((b->n_c + 255) / 256); }
 
 // Number of partials a fused dot product of an apply writes (per value): one
 // per workgroup of the kernel that writes the result.
 int apply_dot_parts(const cpm_band* b, bool transpose) {
-  if (transpose) return grid_for(b->n, 256);
+  if (transpose) return bc_groups(b) + lap_groups(b);
   return lap_row_groups(b) + lap_groups(b);
 }
 
@@ -1051,11 +1120,12 @@ static void launch_lap(const cpm_band* b, const Tune& tn, hipStream_t st, const 
                        const TA* a, TV* v, int64_t ld, int nrhs, double cd, double co,
                        const double* gsum, double gscale, const double* coef, DotOut<TV> dot,
                        int part, const Skip& skip) {
-  LRows lr{b->n_lrows, ALL || part == PART_MAIN ? 0 : lap_row_groups(b), 2 * DIM, b->lrow_id,
-           b->lcol, b->lrow_inst};
+  LRows lr{b->n_lrows, part == PART_MAIN ? 0 : ALL ? bc_groups(b) : lap_row_groups(b), 2 * DIM,
+           b->lrow_id, b->lcol, b->lrow_inst};
+  LPull lp{b->lt_pull, b->bc_lt, b->lt_start, b->lt_src, b->lrow_id, (int)b->n_s, (int)b->n_c};
   const int64_t g = (int64_t)lr.groups + (part == PART_EXPLICIT ? 0 : lap_groups(b));
   if (!g) return;
-  hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g), dim3(256), 0, st, lr,
+  hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g), dim3(256), 0, st, lr, lp,
                      b->blk_face, b->nb, u, a, v, ld, nrhs, cd, co, gsum, gscale, tn.xcd, coef,
                      skip, dot);
   CPM_LAUNCH_CHECK();
@@ -1137,81 +1207,85 @@ void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u, T* 
   else apply_dim<T, 2>(b, m, n, nrhs, u, v, st, gs, gamma, a, nullptr, dy, dpart, skip);
 }
 
-// The transposed apply.  c = (L - diag L)^T w and e = E^T c are FP64 scratch
-// vectors for both storage precisions (the combine step cancels the two
-// terms of size N^2, as the forward Laplacian pass does).
+// Right-hand sides of one transposed gather: its buffer takes CELLS entries a
+// supertile each, so several share it only while it stays small.
+constexpr size_t kTransposeBufBytes = size_t(256) << 20;
+static int transpose_rhs(const cpm_band* b, int nrhs) {
+  const size_t one = sizeof(double) * (size_t)b->nst *
+                     (b->dim == 3 ? Super<3>::CELLS : Super<2>::CELLS);
+  const size_t k = one ? kTransposeBufBytes / one : (size_t)nrhs;
+  return (int)std::max<size_t>(1, std::min<size_t>(k, (size_t)nrhs));
+}
+
+// scratch: c = (L - diag L)^T w, the supertiles' sums, the explicit targets'
+struct TransposeScratch {
+  double *c, *buf, *x;
+  int64_t bufld;
+  int nr;                 // right-hand sides buf and x hold
+};
+static TransposeScratch transpose_scratch(const cpm_band* b, int nrhs) {
+  TransposeScratch t;
+  t.nr = transpose_rhs(b, nrhs);
+  t.bufld = (int64_t)b->nst * (b->dim == 3 ? Super<3>::CELLS : Super<2>::CELLS);
+  t.c = static_cast<double*>(band_scratch(b, 1, sizeof(double) * (size_t)b->n * nrhs));
+  // at least one entry each: lanes without one load the first
+  t.buf = static_cast<double*>(
+      band_scratch(b, 2, sizeof(double) * ((size_t)t.bufld * t.nr + 1)));
+  t.x = static_cast<double*>(
+      band_scratch(b, 5, sizeof(double) * ((size_t)b->n_et * t.nr + 1)));
+  return t;
+}
+void apply_transpose_scratch(const cpm_band* b, int nrhs) { transpose_scratch(b, nrhs); }
+
+// The transposed apply in three launches (the last two once for every few
+// right-hand sides).  c = (L - diag L)^T w and E^T c are FP64 for both storage
+// precisions (the combine step cancels the two terms of size N^2, as the
+// forward Laplacian pass does).
 template <class T, int DIM>
 static void apply_T_dim(const cpm_band* b, double m, double n, int nrhs, const T* w, T* z,
-                        hipStream_t st, const T* dy = nullptr, double* dpart = nullptr) {
+                        hipStream_t st, const T* dy, double* dpart, const Skip& skip) {
+  if (!b->st_pull) CPM_FAIL(CPM_E_INVALID, "this band has no transpose schedule");
   const int64_t ld = b->n;
-  double* c = static_cast<double*>(band_scratch(b, 1, sizeof(double) * (size_t)ld * nrhs));
-  double* e = static_cast<double*>(band_scratch(b, 2, sizeof(double) * (size_t)ld * nrhs));
+  const TransposeScratch t = transpose_scratch(b, nrhs);
   const double N2 = (double)b->N * (double)b->N;
-  const double co = N2;
-  // c = (L - diag L)^T w: symmetric bulk over every PDE row, then corrections
-  // (fill kernels, not memsets: this sequence may be captured into a graph);
-  // k_lap<ALL> writes every PDE entry, so only the BC entries need clearing
-  if (b->n_c)
-    for (int r = 0; r < nrhs; ++r)
-      hipLaunchKernelGGL(k_fill<double>, dim3(grid_for(b->n_c, 256, 4096)), dim3(256), 0, st,
-                         c + r * ld + b->n_s, (int64_t)b->n_c, 0.0);
-  launch_lap<T, T, double, DIM, true, false>(b, tune_of<T>(b), st, w, w, c, ld, nrhs, 0.0, co,
-                                             nullptr, 0.0, nullptr,
-                                             DotOut<double>{nullptr, nullptr, 0}, PART_ALL, Skip{});
-  if (b->lt_tgt) {
-    if (b->n_lt) {
-      hipLaunchKernelGGL(k_lt_pull<T>, dim3(grid_for(b->n_lt, 256)), dim3(256), 0, st, b->n_lt,
-                         b->lt_tgt, b->lt_start, b->lt_src, b->lrow_id, w, c, ld, nrhs, co);
-      CPM_LAUNCH_CHECK();
-    }
-  } else if (b->n_lrows) {
-    CPM_FAIL(CPM_E_INVALID, "this band has no transposed FD pull lists");
-  }
-  // e = E^T c
-  hipLaunchKernelGGL(k_fill<double>, dim3(grid_for(ld * nrhs, 256, 4096)), dim3(256), 0, st, e,
-                     ld * nrhs, 0.0);
-  if (b->ntiles) {
-    if (!b->tile_col) CPM_FAIL(CPM_E_INVALID, "this band has no transpose schedule");
-    for (int r = 0; r < nrhs; ++r)
-      for (int k = 0; k < 8; ++k) {
-        const int cnt = b->col_start[k + 1] - b->col_start[k];
-        if (!cnt) continue;
-        hipLaunchKernelGGL((k_gather_T<T, DIM>), dim3(cnt), dim3(64), 0, st, bview(b), tview(b),
-                           b->tile_col + b->col_start[k], b->N, c, e, ld, r, tune_of<T>(b).xcd);
-        CPM_LAUNCH_CHECK();
-      }
-  }
-  if (b->et_tgt) {
-    if (b->n_et) {
-      for (int r = 0; r < nrhs; ++r)
-        hipLaunchKernelGGL(k_et_pull, dim3((b->n_et + 3) / 4), dim3(256), 0, st, b->n_et,
-                           b->et_tgt, b->et_start, b->et_src, b->et_w, c + r * ld, e + r * ld);
-      CPM_LAUNCH_CHECK();
-    }
-  } else if (b->n_erows) {
-    CPM_FAIL(CPM_E_INVALID, "this band has no transposed interpolation pull lists");
-  }
   const double cd = m + n * (-2.0 * DIM * N2);
-  const int64_t total = ld * nrhs;
-  const int gc = grid_for(total, 256);
-  if (dy) {
-    if ((int64_t)gc * 256 < total) CPM_FAIL(CPM_E_INVALID, "internal: fused dot grid too small");
-    hipLaunchKernelGGL((k_combine<T, true>), dim3(gc), dim3(256), 0, st, w, e, z, cd, n, total,
-                       dy, dpart, gc);
-  } else {
-    hipLaunchKernelGGL((k_combine<T>), dim3(gc), dim3(256), 0, st, w, e, z, cd, n, total,
-                       nullptr, nullptr, 0);
+  const Tune& tn = tune_of<T>(b);
+  launch_lap<T, T, double, DIM, true, false>(b, tn, st, w, w, t.c, ld, nrhs, 0.0, N2, nullptr, 0.0,
+                                             nullptr, DotOut<double>{nullptr, nullptr, 0},
+                                             PART_ALL, skip);
+  constexpr int64_t EG = 8 * kEPullTargets;
+  const EPull ep{b->n_et, (int)((b->n_et + EG - 1) / EG * 8), b->et_start, b->et_src, b->et_w};
+  const BcPull bc{b->bc_et, bc_groups(b), (int)b->n_s, (int)b->n_c};
+  for (int r = 0; r < nrhs; r += t.nr) {
+    const int k = std::min(t.nr, nrhs - r);
+    const int waves = (int64_t)b->nst * k <= kTSplitBelow ? 2 : 1;
+    const int64_t g = (int64_t)ep.groups / waves + b->nst;
+    auto kern = waves == 2 ? k_gather_T<T, DIM, 2> : k_gather_T<T, DIM, 1>;
+    if (g)
+      hipLaunchKernelGGL(kern, dim3((unsigned)g, k), dim3(64 * waves), 0, st, ep, sview(b),
+                         b->st_meta, b->st_rng, t.c, t.x, t.buf, ld, t.bufld, r, tn.xcd, skip);
+    CPM_LAUNCH_CHECK();
+    const dim3 gc((unsigned)(bc.groups + lap_groups(b)), k);
+    if (dy)
+      hipLaunchKernelGGL((k_combine<T, DIM, true>), gc, dim3(256), 0, st, bc, b->blk_face,
+                         b->st_pull, b->nb, t.buf, t.x, t.bufld, b->n_et, w, z, ld, r, cd, n,
+                         tn.xcd, DotOut<T>{dy, dpart, (int)gc.x}, skip);
+    else
+      hipLaunchKernelGGL((k_combine<T, DIM, false>), gc, dim3(256), 0, st, bc, b->blk_face,
+                         b->st_pull, b->nb, t.buf, t.x, t.bufld, b->n_et, w, z, ld, r, cd, n,
+                         tn.xcd, DotOut<T>{nullptr, nullptr, 0}, skip);
+    CPM_LAUNCH_CHECK();
   }
-  CPM_LAUNCH_CHECK();
 }
 
 template <class T>
 void apply_transpose_impl(const cpm_band* b, double m, double n, int nrhs, const T* w, T* z,
                           hipStream_t st, const double*, double gamma, const T* dy,
-                          double* dpart) {
+                          double* dpart, Skip skip) {
   if (gamma != 0.0) CPM_FAIL(CPM_E_INVALID, "the gauge is not supported for the transpose");
-  if (b->dim == 3) apply_T_dim<T, 3>(b, m, n, nrhs, w, z, st, dy, dpart);
-  else apply_T_dim<T, 2>(b, m, n, nrhs, w, z, st, dy, dpart);
+  if (dy && nrhs != 1) CPM_FAIL(CPM_E_INVALID, "internal: fused dots take one right-hand side");
+  if (b->dim == 3) apply_T_dim<T, 3>(b, m, n, nrhs, w, z, st, dy, dpart, skip);
+  else apply_T_dim<T, 2>(b, m, n, nrhs, w, z, st, dy, dpart, skip);
 }
 
 template void apply_impl<double>(const cpm_band*, double, double, int, const double*, double*,
@@ -1220,10 +1294,10 @@ template void apply_impl<float>(const cpm_band*, double, double, int, const floa
                                 hipStream_t, const double*, double, const float*, double*, Skip);
 template void apply_transpose_impl<double>(const cpm_band*, double, double, int, const double*,
                                            double*, hipStream_t, const double*, double,
-                                           const double*, double*);
+                                           const double*, double*, Skip);
 template void apply_transpose_impl<float>(const cpm_band*, double, double, int, const float*,
                                           float*, hipStream_t, const double*, double,
-                                          const float*, double*);
+                                          const float*, double*, Skip);
 
 }  // namespace cpm
 

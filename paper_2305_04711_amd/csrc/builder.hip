@@ -433,9 +433,7 @@ __global__ __launch_bounds__(256) void k_tile_count2(Blocks B, int nb, int N, in
 template <int DIM>
 __global__ __launch_bounds__(256) void k_tile_fill(Blocks B, int nb, int N, int64_t n_s,
                                                    const double* cp, const int* eflag,
-                                                   const int* tile_blk_of, int* pos2, int ntr,
-                                                   int* perm, double* frac64, float* frac32,
-                                                   unsigned* lbase) {
+                                                   const int* tile_blk_of, int* pos2, int* perm) {
   NODE_PROLOGUE(DIM);
   if (eflag[dof]) return;
   const int bb = tile_blk_of[dof];
@@ -444,62 +442,7 @@ __global__ __launch_bounds__(256) void k_tile_fill(Blocks B, int nb, int N, int6
   int base[3];
   double t[3];
   stencil_base<DIM>(y, N, B.p, base, t);
-  const int pos = atomicAdd(&pos2[(int64_t)bb * 64 + local_base_code<DIM>(base)], 1);
-  perm[pos] = dof;
-  for (int a = 0; a < DIM; ++a) {
-    frac64[(int64_t)a * ntr + pos] = t[a];
-    frac32[(int64_t)a * ntr + pos] = (float)t[a];
-  }
-  const unsigned lx = base[0] & (G::BX - 1), ly = base[1] & (G::BX - 1),
-                 lz = DIM == 3 ? (base[2] & (G::BX - 1)) : 0;
-  lbase[pos] = lx | (ly << 8) | (lz << 16);
-}
-
-// Rows that share a tile and a stencil base land in their bucket in the
-// order k_tile_fill's atomics gave them; sort each bucket by DOF so that the
-// tile order (and with it the summation order of the transposed apply's
-// run sums) is the same on every build.  Buckets hold a few rows (the nodes
-// along one normal line), so one thread per bucket sorts by insertion.
-template <int DIM>
-__global__ void k_tile_sort_buckets(int64_t nbk, const int* cnt, const int* end, int ntr,
-                                    int* perm, double* frac64, float* frac32) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nbk;
-       k += (int64_t)gridDim.x * blockDim.x) {
-  if (cnt[k] < 2) continue;
-  const int e = end[k], s = e - cnt[k];
-  for (int i = s + 1; i < e; ++i) {
-    const int key = perm[i];
-    double f64[3];
-    float f32[3];
-    for (int a = 0; a < DIM; ++a) {
-      f64[a] = frac64[(int64_t)a * ntr + i];
-      f32[a] = frac32[(int64_t)a * ntr + i];
-    }
-    int j = i - 1;
-    while (j >= s && perm[j] > key) {
-      perm[j + 1] = perm[j];
-      for (int a = 0; a < DIM; ++a) {
-        frac64[(int64_t)a * ntr + j + 1] = frac64[(int64_t)a * ntr + j];
-        frac32[(int64_t)a * ntr + j + 1] = frac32[(int64_t)a * ntr + j];
-      }
-      --j;
-    }
-    perm[j + 1] = key;
-    for (int a = 0; a < DIM; ++a) {
-      frac64[(int64_t)a * ntr + j + 1] = f64[a];
-      frac32[(int64_t)a * ntr + j + 1] = f32[a];
-    }
-  }
-  }
-}
-
-__global__ void k_tile_compact(const int* cnt, const int* off, const int* tidx, int nb,
-                               int* tile_blk, int* tile_start) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nb && cnt[b] > 0) {
-    tile_blk[tidx[b]] = b;
-    tile_start[tidx[b]] = off[b];
-  }
+  perm[atomicAdd(&pos2[(int64_t)bb * 64 + local_base_code<DIM>(base)], 1)] = dof;
 }
 
 __global__ void k_nonzero(const int* in, int n, int* out) {
@@ -543,7 +486,7 @@ __global__ void k_st_used(int ncell, const int* first, const int* slot0, int* us
 template <int DIM>
 __global__ void k_st_fill(Blocks B, int ncell, const int* first, const int* slot0,
                           const int* used, const int* idx, int4* rng, QMeta* meta) {
-  constexpr int NQ = DIM == 3 ? 18 : 9;
+  constexpr int NQ = Super<DIM>::NB;
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= (int64_t)ncell * NQ) return;
   const int s = (int)(g / NQ), q = (int)(g % NQ);
@@ -559,12 +502,15 @@ __global__ void k_st_fill(Blocks B, int ncell, const int* first, const int* slot
   }
 }
 
-// The rows of a bucket (block of the stencil base, local base; ascending by
-// DOF) into its slots, two at a time.
+// The rows of a bucket (block of the stencil base, local base) into its
+// slots, two at a time, ascending by DOF: k_tile_fill's atomics gave them any
+// order, and the summation order of the transposed apply is to be the same on
+// every build.  Buckets hold a few rows (the nodes along one normal line), so
+// one thread per bucket sorts by insertion.
 template <int DIM>
-__global__ void k_slot_fill(int64_t nbk, const int* cnt, const int* end, const int* slot0,
-                            const int4* coord, int ntr, const int* perm, const double* frac64,
-                            int64_t ns, int2* dof, unsigned short* base, double2* f64,
+__global__ void k_slot_fill(int64_t nbk, int N, int p, int64_t n_s, const double* cp,
+                            const int* cnt, const int* end, const int* slot0, const int4* coord,
+                            int* perm, int64_t ns, int2* dof, unsigned short* base, double2* f64,
                             float2* f32) {
   using G = Geo<DIM>;
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nbk;
@@ -572,21 +518,111 @@ __global__ void k_slot_fill(int64_t nbk, const int* cnt, const int* end, const i
     const int n = cnt[k];
     if (!n) continue;
     const int r0 = end[k] - n, s0 = slot0[k];
+    for (int i = r0 + 1; i < r0 + n; ++i) {
+      const int key = perm[i];
+      int j = i - 1;
+      for (; j >= r0 && perm[j] > key; --j) perm[j + 1] = perm[j];
+      perm[j + 1] = key;
+    }
     const int4 c = coord[k >> 6];
     const int code = (int)(k & 63);
     const int lx = G::lx(code) + G::BX * (c.x & 1), ly = G::ly(code) + G::BX * (c.y & 1),
               lz = DIM == 3 ? G::lz(code) : 0;
     for (int j = 0; j < n; j += 2) {
-      const int i = r0 + j, i2 = j + 1 < n ? i + 1 : i, s = s0 + (j >> 1);
-      dof[s] = make_int2(perm[i], j + 1 < n ? perm[i2] : -1);
+      const int s = s0 + (j >> 1), d0 = perm[r0 + j], d1 = j + 1 < n ? perm[r0 + j + 1] : -1;
+      dof[s] = make_int2(d0, d1);
       base[s] = (unsigned short)(lx | (ly << 4) | (lz << 8));
+      int b0[3];
+      double t0[3], t1[3];
+      stencil_base<DIM>(load_v(cp, n_s, d0, DIM), N, p, b0, t0);
+      stencil_base<DIM>(load_v(cp, n_s, d1 >= 0 ? d1 : d0, DIM), N, p, b0, t1);
       for (int a = 0; a < DIM; ++a) {
-        const double t0 = frac64[(int64_t)a * ntr + i], t1 = frac64[(int64_t)a * ntr + i2];
-        f64[a * ns + s] = make_double2(t0, t1);
-        f32[a * ns + s] = make_float2((float)t0, (float)t1);
+        f64[a * ns + s] = make_double2(t0[a], t1[a]);
+        f32[a * ns + s] = make_float2((float)t0[a], (float)t1[a]);
       }
     }
   }
+}
+
+// supertile of the cell a block lies in, -1 where the cell has no slots
+__global__ void k_st_of_blk(int nb, const int* sid_ex, const int* head, const int* used,
+                            const int* idx, int* st) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= nb) return;
+  const int s = sid_ex[b] + head[b] - 1;   // cells are numbered by their heads
+  st[b] = used[s] ? idx[s] : -1;
+}
+
+// Per block, the supertiles whose cubes reach it and where its nodes' sums
+// lie in the buffer (entries 0 .. 2^d - 1, in a fixed order).
+template <int DIM>
+__global__ void k_st_pull(Blocks B, int nb, const int* st_of_blk, const QMeta* meta, Pull* pull) {
+  using SP = Super<DIM>;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int i = (int)(g >> 3), k = (int)(g & 7);
+  if (i >= nb) return;
+  const int4 c = B.coord[i];
+  // along x and y a block is the first (even), second (odd) or third (even)
+  // of a cube's three; along z the first or second of two
+  const int kx = k & 1, ky = (k >> 1) & 1, kz = k >> 2;
+  Pull out{0ull, 0};
+  const bool odd_x = c.x & 1, odd_y = c.y & 1;
+  if (!(odd_x && kx) && !(odd_y && ky) && (DIM == 3 || !kz)) {
+    const int sx = (c.x >> 1) - kx, sy = (c.y >> 1) - ky, z = c.z - kz;
+    int st = -1;
+    for (int j = 0; j < 4 && st < 0; ++j) {
+      const int id = hash_find(B.hkeys, B.hvals, B.hcap,
+                               block_key(2 * sx + (j & 1), 2 * sy + (j >> 1), z));
+      if (id >= 0) st = st_of_blk[id];
+    }
+    if (st >= 0) {
+      const int q = (c.x - 2 * sx) + 3 * (c.y - 2 * sy) + 9 * kz;
+      const QMeta* m = meta + (int64_t)st * SP::NB;
+      out.off = (long long)st * SP::CELLS;
+      for (int o = 0; o < q; ++o) out.off += __popcll(m[o].mask & SP::inside(o));
+      out.mask = m[q].mask & SP::inside(q);
+    }
+  }
+  pull[(int64_t)i * 9 + k] = out;
+}
+
+__device__ __forceinline__ int lower_bound_i32(const int* a, int n, int key) {
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (a[mid] < key) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Per block, the slots whose DOF is in the ascending list tgt and the first
+// one's place in it.
+__global__ void k_tgt_blocks(int nb, const unsigned long long* mask, const int* off, const int* tgt,
+                             int n_tgt, Pull* out, int stride) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= nb) return;
+  const unsigned long long m = mask[b];
+  const int d0 = off[b], d1 = d0 + __popcll(m);
+  const int k0 = lower_bound_i32(tgt, n_tgt, d0);
+  unsigned long long t = 0ull;
+  int k = k0, d = d0;
+  for (int s = 0; s < 64 && k < n_tgt && tgt[k] < d1; ++s)
+    if ((m >> s) & 1ull) {
+      if (tgt[k] == d) {
+        t |= 1ull << s;
+        ++k;
+      }
+      ++d;
+    }
+  out[(int64_t)b * stride] = Pull{t, t ? (long long)k0 : 0};
+}
+
+__global__ void k_tgt_bc(int64_t n_s, int64_t n_c, const int* tgt, int n_tgt, int* out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n_c) return;
+  const int d = (int)(n_s + i), k = lower_bound_i32(tgt, n_tgt, d);
+  out[i] = k < n_tgt && tgt[k] == d ? k : -1;
 }
 
 // Explicit interpolation rows of swapped PDE rows.
@@ -596,7 +632,7 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
                                                   const int* alpha_of, const double* side_v,
                                                   const int* eflag, const int* eidx,
                                                   int* erow_id, int* ecol, double* ew,
-                                                  float* ew32, int* ebase) {
+                                                  int* ebase) {
   NODE_PROLOGUE(DIM);
   constexpr int NM = DIM == 3 ? 64 : 16;
   if (!eflag[dof]) return;
@@ -619,7 +655,6 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
     if (o >= nmp) {   // quadratic stencils fill the first (p+1)^d slots
       ecol[(int64_t)r * NM + o] = -1;
       ew[(int64_t)r * NM + o] = 0.0;
-      ew32[(int64_t)r * NM + o] = 0.0f;
       continue;
     }
     const int a = o % np, b = (o / np) % np, c = o / (np * np);
@@ -630,7 +665,6 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
     const double wt = DIM == 3 ? (w[2][c] * w[1][b]) * w[0][a] : w[1][b] * w[0][a];
     ecol[(int64_t)r * NM + o] = j;
     ew[(int64_t)r * NM + o] = wt;
-    ew32[(int64_t)r * NM + o] = (float)wt;
   }
 }
 
@@ -651,7 +685,7 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
                           cpm_surface S, IBCList L, const int* bc_node, const double* bc_cpc,
                           const int* bc_side, const int* bc_curve, const int* bc_k,
                           const int* row_c, const int* alpha_of, const double* side_v, int r0,
-                          int* erow_id, int* ecol, double* ew, float* ew32, int* ebase,
+                          int* erow_id, int* ecol, double* ew, int* ebase,
                           double* ecoef, unsigned long long* counters) {
   using G = Geo<DIM>;
   constexpr int NM = DIM == 3 ? 64 : 16;
@@ -666,7 +700,6 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
     for (int o = 0; o < NM; ++o) {
       ecol[(int64_t)r * NM + o] = -1;
       ew[(int64_t)r * NM + o] = 0.0;
-      ew32[(int64_t)r * NM + o] = 0.0f;
     }
     for (int a = 0; a < DIM; ++a) ebase[r * DIM + a] = 0;
     return;
@@ -694,7 +727,6 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
     if (o >= nmp) {
       ecol[(int64_t)r * NM + o] = -1;
       ew[(int64_t)r * NM + o] = 0.0;
-      ew32[(int64_t)r * NM + o] = 0.0f;
       continue;
     }
     const int a = o % np, b = (o / np) % np, c = o / (np * np);
@@ -708,7 +740,6 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
     const double wt = sgn * (DIM == 3 ? (w[2][c] * w[1][b]) * w[0][a] : w[1][b] * w[0][a]);
     ecol[(int64_t)r * NM + o] = m;
     ew[(int64_t)r * NM + o] = wt;
-    ew32[(int64_t)r * NM + o] = (float)wt;
   }
   if (holes) atomicAdd(&counters[3], (unsigned long long)holes);
 }
@@ -801,33 +832,7 @@ __global__ void k_lrow_bc(Blocks B, int N, cpm_surface S, IBCList L, int64_t n_s
   }
 }
 
-// Per-tile metadata of the staged blocks and per-block Laplacian metadata.
-__global__ void k_tile_meta(Blocks B, int ntiles, int nq, int nnbr, const int* tile_blk,
-                            QMeta* meta) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (int64_t)ntiles * 8) return;
-  const int t = (int)(g >> 3), q = (int)(g & 7);
-  QMeta m{0ull, 0, -1};
-  if (q < nq) {
-    const int qx = q & 1, qy = (q >> 1) & 1, qz = q >> 2;
-    const int tb = tile_blk[t];
-    const int code = nnbr == 27 ? (qz + 1) * 9 + (qy + 1) * 3 + (qx + 1) : (qy + 1) * 3 + (qx + 1);
-    const int id = q == 0 ? tb : B.nbr[tb * nnbr + code];
-    if (id >= 0) m = QMeta{B.mask[id], B.off[id], id};
-  }
-  meta[g] = m;
-}
-
-// Parity class of a tile's block: two tiles of one class stage disjoint
-// sets of blocks (their block coordinates differ by at least 2 along some
-// axis, and a tile stages its block and the next one along each axis).
-__global__ void k_tile_colour(int ntiles, const int* tile_blk, const int4* coord, int* colour) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ntiles) return;
-  const int4 c = coord[tile_blk[t]];
-  colour[t] = (c.x & 1) | ((c.y & 1) << 1) | ((c.z & 1) << 2);
-}
-
+// Per-block Laplacian metadata.
 __global__ void k_blk_face(Blocks B, int nb, int dim, int nnbr, const unsigned long long* lrow_mask,
                            QMeta* face) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -982,15 +987,13 @@ __global__ void k_pull_pairs_l(int nrows, int nf, int64_t n_s, const int* row_id
   val[g] = 2 * i + sgn;
 }
 
-// E pull entries in sorted order: the source's weights (both precisions) and
-// its row's DOF, which replaces the source index in place
+// E pull entries in sorted order: the source's weight and its row's DOF, which replaces the source index in place
 __global__ void k_pull_denorm_e(int total, int* src, int nm, const int* erow_id, const double* ew,
-                                const float* ew32, double* w64, float* w32) {
+                                double* w64) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int g = src[e];
   w64[e] = ew[g];
-  w32[e] = ew32[g];
   src[e] = erow_id[g / nm];
 }
 
@@ -1350,19 +1353,18 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
     b->erow_id = b->alloc<int>(b->n_erows);
     b->ecol = b->alloc<int>((size_t)b->n_erows * NM);
     b->ew = b->alloc<double>((size_t)b->n_erows * NM);
-    b->ew32 = b->alloc<float>((size_t)b->n_erows * NM);
     b->ebase = b->alloc<int>((size_t)b->n_erows * DIM);
     if (ne_pde)
       hipLaunchKernelGGL(k_erow_pde<DIM>, gnode, dim3(256), 0, st, B, nb, N, n_s, b->cp, row_c.p,
                          alpha_of.p, side_v.p, eflag.p, eidx.p, b->erow_id, b->ecol, b->ew,
-                         b->ew32, b->ebase);
+                         b->ebase);
     CPM_LAUNCH_CHECK();
     b->bc_ecoef = b->alloc<double>(n_c);
     if (n_c)
       hipLaunchKernelGGL(k_erow_bc<DIM>, dim3(grid_for(n_c, 128)), dim3(128), 0, st, B, N, n_s,
                          n_c, b->order, S, L, b->bc_node, b->bc_cpc, b->bc_side, b->bc_curve,
                          bc_kp->p, row_c.p, alpha_of.p, side_v.p, (int)ne_pde, b->erow_id,
-                         b->ecol, b->ew, b->ew32, b->ebase, b->bc_ecoef, counters.p);
+                         b->ecol, b->ew, b->ebase, b->bc_ecoef, counters.p);
     CPM_LAUNCH_CHECK();
     unsigned long long hc[4];
     CPM_HIP(hipMemcpyAsync(hc, counters.p, sizeof(hc), hipMemcpyDeviceToHost, st));
@@ -1377,20 +1379,9 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
     hipLaunchKernelGGL(k_nonzero, dim3(grid_for(nb, 256)), dim3(256), 0, st, tile_cnt.p, nb, nz.p);
     CPM_LAUNCH_CHECK();
     b->ntiles = (int)scan_exclusive_i32(nz.p, tidx.p, nb, st, b->da);
-    b->tile_blk = b->alloc<int>(b->ntiles);
-    b->tile_start = b->alloc<int>(b->ntiles + 1);
-    hipLaunchKernelGGL(k_tile_compact, dim3(grid_for(nb, 256)), dim3(256), 0, st, tile_cnt.p,
-                       tile_off.p, tidx.p, nb, b->tile_blk, b->tile_start);
-    CPM_LAUNCH_CHECK();
-    CPM_HIP(hipMemcpyAsync(b->tile_start + b->ntiles, &b->n_tile_rows, sizeof(int),
-                           hipMemcpyHostToDevice, st));
     const int ntr = b->n_tile_rows;
-    b->perm = b->alloc<int>(ntr);
-    b->frac64 = b->alloc<double>((size_t)DIM * ntr);
-    b->frac32 = b->alloc<float>((size_t)DIM * ntr);
-    b->lbase = b->alloc<unsigned>(ntr);
     {
-      Tmp<int> cnt2(b, (size_t)nb * 64), pos2(b, (size_t)nb * 64);
+      Tmp<int> cnt2(b, (size_t)nb * 64), pos2(b, (size_t)nb * 64), perm(b, ntr);
       CPM_HIP(hipMemsetAsync(cnt2.p, 0, (size_t)nb * 64 * sizeof(int), st));
       hipLaunchKernelGGL(k_tile_count2<DIM>, gnode, dim3(256), 0, st, B, nb, N, n_s, b->cp,
                          eflag.p, tile_blk_of.p, cnt2.p);
@@ -1398,12 +1389,7 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       const int64_t tot = scan_exclusive_i32(cnt2.p, pos2.p, (int64_t)nb * 64, st, b->da);
       if (tot != ntr) CPM_FAIL(CPM_E_INVALID, "internal: tile row count mismatch");
       hipLaunchKernelGGL(k_tile_fill<DIM>, gnode, dim3(256), 0, st, B, nb, N, n_s, b->cp,
-                         eflag.p, tile_blk_of.p, pos2.p, ntr, b->perm, b->frac64, b->frac32,
-                         b->lbase);
-      CPM_LAUNCH_CHECK();
-      hipLaunchKernelGGL(k_tile_sort_buckets<DIM>, dim3(grid_for((int64_t)nb * 64, 256)),
-                         dim3(256), 0, st, (int64_t)nb * 64, cnt2.p, pos2.p, ntr, b->perm,
-                         b->frac64, b->frac32);
+                         eflag.p, tile_blk_of.p, pos2.p, perm.p);
       CPM_LAUNCH_CHECK();
       // slots of two rows, and the supertiles that hold them
       const int64_t nbk = (int64_t)nb * 64;
@@ -1427,7 +1413,7 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
                          slot0.p, used.p);
       CPM_LAUNCH_CHECK();
       b->nst = (int)scan_exclusive_i32(used.p, idx.p, ncell, st, b->da);
-      constexpr int NQ = DIM == 3 ? 18 : 9;
+      constexpr int NQ = Super<DIM>::NB;
       b->st_meta = b->alloc<QMeta>((size_t)b->nst * NQ);
       b->st_rng = b->alloc<int4>(b->nst);
       b->slot_dof = b->alloc<int2>(b->n_slots);
@@ -1437,9 +1423,17 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       hipLaunchKernelGGL(k_st_fill<DIM>, dim3((unsigned)(((int64_t)ncell * NQ + 255) / 256)),
                          dim3(256), 0, st, B, ncell, first.p, slot0.p, used.p, idx.p, b->st_rng,
                          b->st_meta);
-      hipLaunchKernelGGL(k_slot_fill<DIM>, dim3(grid_for(nbk, 256)), dim3(256), 0, st, nbk, cnt2.p,
-                         pos2.p, slot0.p, b->blk_coord, ntr, b->perm, b->frac64, b->n_slots,
-                         b->slot_dof, b->slot_base, b->slot_frac64, b->slot_frac32);
+      hipLaunchKernelGGL(k_slot_fill<DIM>, dim3(grid_for(nbk, 256)), dim3(256), 0, st, nbk, N,
+                         b->p, n_s, b->cp, cnt2.p, pos2.p, slot0.p, b->blk_coord, perm.p,
+                         b->n_slots, b->slot_dof, b->slot_base, b->slot_frac64, b->slot_frac32);
+      CPM_LAUNCH_CHECK();
+      // what each block takes from the transposed gather
+      Tmp<int> st_of(b, nb);
+      hipLaunchKernelGGL(k_st_of_blk, dim3(grid_for(nb, 256)), dim3(256), 0, st, nb, sid.p, head.p,
+                         used.p, idx.p, st_of.p);
+      b->st_pull = b->alloc<Pull>((size_t)nb * 9);
+      hipLaunchKernelGGL(k_st_pull<DIM>, dim3((unsigned)(((int64_t)nb * 8 + 255) / 256)), dim3(256),
+                         0, st, B, nb, st_of.p, b->st_meta, b->st_pull);
       CPM_LAUNCH_CHECK();
       CPM_HIP(hipStreamSynchronize(st));
     }
@@ -1488,9 +1482,8 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       CPM_HIP(hipStreamSynchronize(st));
       b->n_et_entries = total;
       b->et_w = b->alloc<double>(total);
-      b->et_w32 = b->alloc<float>(total);
       hipLaunchKernelGGL(k_pull_denorm_e, dim3(grid_for(total, 256)), dim3(256), 0, st, total,
-                         b->et_src, NM, b->erow_id, b->ew, b->ew32, b->et_w, b->et_w32);
+                         b->et_src, NM, b->erow_id, b->ew, b->et_w);
       CPM_LAUNCH_CHECK();
     }
     const int64_t nl = (int64_t)b->n_lrows * 2 * DIM * 2;
@@ -1502,37 +1495,22 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
     }
     build_pull(b, nl, keyl, vall, st, b->n_lt, b->lt_tgt, b->lt_start, b->lt_src);
   }
-  // metadata read by the apply kernels
-  b->tile_meta = b->alloc<QMeta>((size_t)b->ntiles * 8);
-  if (b->ntiles)
-    hipLaunchKernelGGL(k_tile_meta, dim3(grid_for((int64_t)b->ntiles * 8, 256)), dim3(256), 0, st,
-                       B, b->ntiles, 1 << DIM, G::NNBR, b->tile_blk, b->tile_meta);
-  CPM_LAUNCH_CHECK();
-  // transpose schedule: tiles grouped by parity class (stable in tile order)
-  b->tile_col = b->alloc<int4>(b->ntiles);
-  std::fill(b->col_start, b->col_start + 9, 0);
-  if (b->ntiles) {
-    Tmp<int> colour(b, b->ntiles);
-    hipLaunchKernelGGL(k_tile_colour, dim3(grid_for(b->ntiles, 256)), dim3(256), 0, st, b->ntiles,
-                       b->tile_blk, b->blk_coord, colour.p);
-    CPM_LAUNCH_CHECK();
-    std::vector<int> hcol(b->ntiles), hstart(b->ntiles + 1);
-    std::vector<int4> order(b->ntiles);
-    CPM_HIP(hipMemcpyAsync(hcol.data(), colour.p, sizeof(int) * b->ntiles, hipMemcpyDeviceToHost,
-                           st));
-    CPM_HIP(hipMemcpyAsync(hstart.data(), b->tile_start, sizeof(int) * (b->ntiles + 1),
-                           hipMemcpyDeviceToHost, st));
-    CPM_HIP(hipStreamSynchronize(st));
-    for (int t = 0; t < b->ntiles; ++t) ++b->col_start[hcol[t] + 1];
-    for (int k = 0; k < 8; ++k) b->col_start[k + 1] += b->col_start[k];
-    int next[8];
-    std::copy(b->col_start, b->col_start + 8, next);
-    for (int t = 0; t < b->ntiles; ++t)
-      order[next[hcol[t]]++] = make_int4(t, hstart[t], hstart[t + 1], 0);
-    CPM_HIP(hipMemcpyAsync(b->tile_col, order.data(), sizeof(int4) * b->ntiles,
-                           hipMemcpyHostToDevice, st));
-    CPM_HIP(hipStreamSynchronize(st));
+  // the explicit rows' targets, block by block
+  b->lt_pull = b->alloc<Pull>(nb);
+  b->bc_et = b->alloc<int>(n_c);
+  b->bc_lt = b->alloc<int>(n_c);
+  hipLaunchKernelGGL(k_tgt_blocks, dim3(grid_for(nb, 256)), dim3(256), 0, st, nb, b->blk_mask,
+                     b->blk_off, b->et_tgt, b->n_et, b->st_pull + 8, 9);
+  hipLaunchKernelGGL(k_tgt_blocks, dim3(grid_for(nb, 256)), dim3(256), 0, st, nb, b->blk_mask,
+                     b->blk_off, b->lt_tgt, b->n_lt, b->lt_pull, 1);
+  if (n_c) {
+    hipLaunchKernelGGL(k_tgt_bc, dim3(grid_for(n_c, 256)), dim3(256), 0, st, n_s, n_c, b->et_tgt,
+                       b->n_et, b->bc_et);
+    hipLaunchKernelGGL(k_tgt_bc, dim3(grid_for(n_c, 256)), dim3(256), 0, st, n_s, n_c, b->lt_tgt,
+                       b->n_lt, b->bc_lt);
   }
+  CPM_LAUNCH_CHECK();
+  // metadata read by the apply kernels
   b->blk_face = b->alloc<QMeta>((size_t)nb * 8);
   hipLaunchKernelGGL(k_blk_face, dim3(grid_for((int64_t)nb * 8, 256)), dim3(256), 0, st, B, nb,
                      DIM, G::NNBR, b->lrow_mask, b->blk_face);

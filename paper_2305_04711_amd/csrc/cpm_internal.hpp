@@ -99,6 +99,45 @@ struct QMeta {
   int pad;
 };
 
+// The slots of a block (mask) that have an entry in some buffer, one after
+// the other from off.
+struct Pull {
+  unsigned long long mask;
+  long long off;
+};
+
+// Supertiles stage the blocks from their corner on, 3 x 3 x 2 (2-D: 3 x 3);
+// the last node along each axis is beyond every stencil.  Slots of staged
+// block q that are inside, and the nodes inside altogether (at most).
+template <int DIM> struct Super {
+  static constexpr int EX = 3 * Geo<DIM>::BX - 1;              // staged edge, x and y
+  static constexpr int EZ = DIM == 3 ? 2 * Geo<3>::BX - 1 : 1; // staged edge, z
+  static constexpr int NB = DIM == 3 ? 18 : 9;                 // staged blocks
+  static constexpr int CELLS = EX * EX * EZ;
+  __host__ __device__ static constexpr unsigned long long inside(int q) {
+    unsigned long long in = 0ull;
+    constexpr int BX = DIM == 3 ? 4 : 8;
+    for (int s = 0; s < 64; ++s) {
+      const int x = DIM == 3 ? s & 3 : s & 7, y = DIM == 3 ? (s >> 2) & 3 : s >> 3,
+                z = DIM == 3 ? s >> 4 : 0;
+      const bool out = (q % 3 == 2 && x == BX - 1) || ((q / 3) % 3 == 2 && y == BX - 1) ||
+                       (DIM == 3 && q / 9 == 1 && z == BX - 1);
+      if (!out) in |= 1ull << s;
+    }
+    return in;
+  }
+};
+
+// the same for every block, evaluated at compile time
+template <int DIM> struct InsideMasks {
+  unsigned long long m[18];
+};
+template <int DIM> constexpr InsideMasks<DIM> inside_masks() {
+  InsideMasks<DIM> t{};
+  for (int q = 0; q < Super<DIM>::NB; ++q) t.m[q] = Super<DIM>::inside(q);
+  return t;
+}
+
 // Launch variants of the apply kernels (chosen by the autotuner).
 struct Tune {
   int pad = 1;     // LDS x-line padding of the staged cube (elements)
@@ -147,21 +186,9 @@ struct cpm_band {
   // PDE rows
   double* cp = nullptr;               // [dim][n_s] stored cp_S (SoA)
 
-  // gather tiles: PDE rows without swapped interpolation members, grouped by
-  // the block that holds their stencil base
+  // tiles: the blocks that hold the stencil base of some PDE row without
+  // swapped interpolation members (a tile row)
   int ntiles = 0, n_tile_rows = 0;
-  int* tile_blk = nullptr;            // [ntiles]
-  cpm::QMeta* tile_meta = nullptr;    // [ntiles][8] the 2^d staged blocks
-  int* tile_start = nullptr;          // [ntiles + 1]
-  int* perm = nullptr;                // [n_tile_rows] row DOF
-  double* frac64 = nullptr;           // [dim][n_tile_rows] FP64 fractions
-  float* frac32 = nullptr;            // [dim][n_tile_rows] FP32 fractions
-  unsigned int* lbase = nullptr;      // [n_tile_rows] packed local base
-  // tiles grouped by the parity class of their block (k_tile_colour): class
-  // k is tile_col[col_start[k] .. col_start[k + 1]), each entry {tile, first
-  // row, end row, 0} (the tile's range in the tile-row arrays)
-  int4* tile_col = nullptr;           // [ntiles]
-  int col_start[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 
   // supertiles: the tile rows whose stencil bases lie in 2 x 2 neighbouring
   // blocks (x and y), two rows of one stencil base to a slot.  Slots are grouped by
@@ -176,13 +203,21 @@ struct cpm_band {
                                       // corner, 4 bits per axis
   double2* slot_frac64 = nullptr;     // [dim][n_slots]
   float2* slot_frac32 = nullptr;      // [dim][n_slots]
+  // The transposed gather adds each supertile's rows up in its staged cube
+  // and stores the sums of the blocks' nodes one after the other in its part
+  // of a buffer.  st_pull: per block of PDE DOFs what it takes from there,
+  // [nb][9] {mask, first entry}: up to 2^d supertiles (of the blocks' nodes
+  // inside their cubes), then its targets among the explicit rows' (et_tgt).
+  cpm::Pull* st_pull = nullptr;
+  int* bc_et = nullptr;               // [n_c] explicit E target of a BC DOF, or -1
+  cpm::Pull* lt_pull = nullptr;       // [nb] the block's explicit FD targets (lt_tgt)
+  int* bc_lt = nullptr;               // [n_c] explicit FD target of a BC DOF, or -1
 
   // rows with explicit interpolation stencils (swapped PDE rows, BC rows)
   int n_erows = 0;
   int* erow_id = nullptr;             // [n_erows]
   int* ecol = nullptr;                // [n_erows][4^dim]
   double* ew = nullptr;               // [n_erows][4^dim]
-  float* ew32 = nullptr;              // [n_erows][4^dim]
   int* ebase = nullptr;               // [n_erows][dim]
 
   // rows with explicit FD stencils (swapped PDE rows, BC rows)
@@ -194,14 +229,13 @@ struct cpm_band {
   // pull lists of the transposed explicit rows (single bands; a batch's
   // composite has none: batches apply only the forward operator): target DOFs, segment
   // starts and sources in ascending order per target.  E: per entry the DOF
-  // of its row and its weight (et_src, et_w, et_w32; sources i * 4^d + o,
+  // of its row and its weight (et_src, et_w; sources i * 4^d + o,
   // entry o of explicit E row i, in ascending order).  L: source 2 i + s,
   // explicit FD row i, s = 1 for the subtracted unswapped column of a
   // swapped PDE entry.
   int n_et = 0, n_lt = 0, n_et_entries = 0;
   int *et_tgt = nullptr, *et_start = nullptr, *et_src = nullptr;
   double* et_w = nullptr;
-  float* et_w32 = nullptr;
   int *lt_tgt = nullptr, *lt_start = nullptr, *lt_src = nullptr;
 
   // BC DOFs
@@ -276,7 +310,9 @@ template <class T>
 void apply_transpose_impl(const cpm_band* b, double m, double n, int nrhs,
                           const T* w, T* z, hipStream_t s,
                           const double* gauge_sum = nullptr, double gamma = 0.0,
-                          const T* dy = nullptr, double* dpart = nullptr);
+                          const T* dy = nullptr, double* dpart = nullptr, Skip skip = {});
+// makes the scratch of apply_transpose_impl (before a graph capture)
+void apply_transpose_scratch(const cpm_band* b, int nrhs);
 int apply_dot_parts(const cpm_band* b, bool transpose);
 // bytes of the forward apply's scratch vector (the FP64 intermediate a = E u)
 size_t apply_scratch_bytes(const cpm_band* b, int nrhs);

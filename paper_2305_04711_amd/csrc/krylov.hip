@@ -466,10 +466,7 @@ struct Bicg {
       band_scratch(b, 3, sizeof(double) * 256 + 64);
       band_scratch(b, 4, sizeof(double) + 64);
     }
-    if (transpose) {
-      band_scratch(b, 1, sizeof(double) * (size_t)n);
-      band_scratch(b, 2, sizeof(double) * (size_t)n);
-    }
+    if (transpose) apply_transpose_scratch(b, 1);
   }
   ~Bicg() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
@@ -479,10 +476,9 @@ struct Bicg {
   // out once the scalars q say that the recurrence has ended
   void apply(const T* in, T* out, const T* dy = nullptr, const Scal* q = nullptr) {
     double* dp = dy ? dpart : nullptr;
-    if (transpose) apply_transpose_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp);
-    else
-      apply_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp,
-                    Skip{q ? &q->done : nullptr, 1, 1});
+    const Skip skip{q ? &q->done : nullptr, 1, 1};
+    if (transpose) apply_transpose_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp, skip);
+    else apply_impl<T>(b, m, nn, 1, in, out, st, nullptr, gamma, dy, dp, skip);
   }
 
   // r = rhs - A x, rh = r, and the scalars of a recurrence that starts there
