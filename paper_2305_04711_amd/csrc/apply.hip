@@ -208,9 +208,13 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s, const 
   }
 }
 
-// Pass 1 in one launch of single wavefronts: the first er.groups take
-// explicit rows, the others a supertile each (er.groups is a multiple of 8,
-// so both parts keep the XCD of a workgroup id).
+// Pass 1 in one launch of single wavefronts: the first sv.n take a supertile
+// each, the last er.groups explicit rows.  Those are short and fill the chip
+// while the last supertiles end: first in the grid they cost the whole apply
+// 22.6, 149 and 756 us against 18.2, 143 and 745 us (sphere at h = 1/64, FP64,
+// and 1/256, FP32; torus at 1/512, FP64).  Two, three or four wavefronts to a
+// supertile, with the staging shared, are slower at every size (20.4 to 21.0
+// us at 1/64).
 //
 // What bounds it: with one tile per wavefront and one row per lane every row
 // read its 4^d members from LDS by itself, at 128 B a clock and CU, with 71%
@@ -238,12 +242,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   __shared__ double s_u[CS + 1];
   const int lane = threadIdx.x;
   int g = blockIdx.x;
-  if (g < er.groups) {
+  if (g >= sv.n) {
+    g -= sv.n;
     if (xcd) g = xcd_remap(g, er.groups);
     explicit_rows<TS, DIM>(er, g, lane, u, a, ld, nrhs, skip);
     return;
   }
-  g -= er.groups;
   if (xcd) g = xcd_remap(g, sv.n);
   const int4 rg = rng[g];
   // the staged blocks' masks and first DOFs: block q's in lane q
