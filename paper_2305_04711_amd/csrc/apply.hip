@@ -99,9 +99,9 @@ template <int DIM> constexpr int erows_per_group() {
 template <class TS, int DIM>
 __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lane,
                                               const TS* __restrict__ u, double* __restrict__ a,
-                                              int64_t ld, int nrhs, const Skip& skip) {
+                                              int64_t ld, int r0, int r1, const Skip& skip) {
   constexpr int M = DIM == 3 ? 64 : 16, RPW = 64 / M;
-  if (!er.inst && nrhs == 1 && skipped(skip, 0, 0)) return;
+  if (!er.inst && r1 == r0 + 1 && skipped(skip, r0, 0)) return;
   const int o = lane & (M - 1);
   int row[kERowPasses], c[kERowPasses];
   double w[kERowPasses];
@@ -113,7 +113,7 @@ __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lan
     c[j] = er.col[e];
     w[j] = er.w[e];
   }
-  for (int r = 0; r < nrhs; ++r) {
+  for (int r = r0; r < r1; ++r) {
     // every lane loads (an absent member's lane entry 0, which it drops), so
     // that no load waits behind a branch for the one before it
     double v[kERowPasses];
@@ -208,13 +208,11 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s, const 
   }
 }
 
-// Pass 1 in one launch of single wavefronts: the first sv.n take a supertile
-// each, the last er.groups explicit rows.  Those are short and fill the chip
+// Pass 1 in one launch, W wavefronts to a workgroup: the first sv.n take a
+// supertile each, the last ones explicit rows.  Those are short and fill the chip
 // while the last supertiles end: first in the grid they cost the whole apply
 // 22.6, 149 and 756 us against 18.2, 143 and 745 us (sphere at h = 1/64, FP64,
-// and 1/256, FP32; torus at 1/512, FP64).  Two, three or four wavefronts to a
-// supertile, with the staging shared, are slower at every size (20.4 to 21.0
-// us at 1/64).
+// and 1/256, FP32; torus at 1/512, FP64).
 //
 // What bounds it: with one tile per wavefront and one row per lane every row
 // read its 4^d members from LDS by itself, at 128 B a clock and CU, with 71%
@@ -230,22 +228,40 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s, const 
 // wavefronts that wait for one another hold their slots idle.
 // Registers, not LDS, set the occupancy (4 or 5 wavefronts per SIMD, which
 // time the same); forcing a sixth spills and loses.
-template <class TS, int DIM, int PAD, int NP>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_gather(
+// Two wavefronts share a supertile where supertiles are few or take several
+// right-hand sides in turn: half the chain of each, next to a barrier.
+// Transpose of one column, one wavefront, two: 28.6, 21.8 us at 600
+// supertiles; 45.6, 41.7 at 2300; 60.6, 60.6 at 4500; 100, 109 at 9100 (two
+// fill and clear two cubes).  Forward apply: 18.3, 17.9 us at 2000; 20.6, 19.3
+// at 2300; 29.9, 29.9 at 4500; 47.0, 47.8 at 9100; of three columns 34.4, 31.4
+// at 1100; 63.4, 61.6 at 4500; 323, 306 at 20000 (FP64 spheres and tori).
+constexpr int kSplitBelow = 4096;
+// Right-hand sides go to workgroups of their own while there are fewer
+// supertiles than this in flight (eight columns, in turn and apart: 58 and 39
+// us at 600 supertiles, 21 and 14 us in 2-D at 40; five: 54 and 56 us at
+// 2000), and in pass 1 of a solver, whose systems end at different times
+// (batched solve of 18 systems: 220 and 195 ms).
+constexpr int kFillSupertiles = 2048, kMaxRhsGroups = 4096;
+template <class TS, int DIM, int PAD, int NP, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ? 4 : 5))) void k_gather(
     ERows er, SuperView sv, const QMeta* __restrict__ meta, const int4* __restrict__ rng,
-    const TS* __restrict__ u, double* __restrict__ a, int64_t ld, int nrhs, int xcd, Skip skip) {
+    const TS* __restrict__ u, double* __restrict__ a, int64_t ld, int nrhs, int per, int xcd,
+    Skip skip) {
   using G = Geo<DIM>;
   using SP = Super<DIM>;
   constexpr int EX = SP::EX, EP = EX + PAD, BX = G::BX, NB = SP::NB;
   constexpr InsideMasks<DIM> IN = inside_masks<DIM>();
   constexpr int CS = SP::EZ * EX * EP;
   __shared__ double s_u[CS + 1];
-  const int lane = threadIdx.x;
+  constexpr int NQ = (NB + W - 1) / W;   // blocks staged by a wave
+  const int lane = threadIdx.x & 63;
+  const int wv = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = blockIdx.y * per, r1 = min(nrhs, r0 + per);
   int g = blockIdx.x;
   if (g >= sv.n) {
     g -= sv.n;
-    if (xcd) g = xcd_remap(g, er.groups);
-    explicit_rows<TS, DIM>(er, g, lane, u, a, ld, nrhs, skip);
+    if (xcd) g = xcd_remap(g, er.groups / W);
+    explicit_rows<TS, DIM>(er, g * W + wv, lane, u, a, ld, r0, r1, skip);
     return;
   }
   if (xcd) g = xcd_remap(g, sv.n);
@@ -268,34 +284,40 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   };
   int cell0 = DIM == 3 ? (G::lz(lane) * EX + G::ly(lane)) * EP + G::lx(lane)
                        : G::ly(lane) * EP + G::lx(lane);
-  for (int r = 0; r < nrhs; ++r) {
+  for (int r = r0; r < r1; ++r) {
     // keeps the cells of all staged blocks from living in registers throughout
     asm volatile("" : "+v"(cell0));
     if (skipped(skip, r, rg.z)) continue;
     // the first pass's row data is requested before the staging loads
-    rows(lane);
+    rows(64 * wv + lane);
     __syncthreads();   // the previous right-hand side's rows are done
     // Every lane loads (an absent node's lane the block's first value, which
     // it drops): under a condition each load would be a basic block of its
     // own and wait for the one before it.
     // Cells of absent nodes hold that value: no tile row's stencil has one.
     const TS* ur = u + r * ld;
-    TS x[NB];
+    TS x[NQ];
 #pragma unroll
-    for (int q = 0; q < NB; ++q) x[q] = ur[lane_i32(qm.z, q) + (int64_t)lane_rank(qmask(q))];
+    for (int j = 0; j < NQ; ++j) {
+      const int q = min(j * W + wv, NB - 1);
+      x[j] = ur[lane_i32(qm.z, q) + (int64_t)lane_rank(qmask(q))];
+    }
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
+    for (int j = 0; j < NQ; ++j) {
+      const int q = min(j * W + wv, NB - 1);
       const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
-      const unsigned long long in = IN.m[q];
       const int off = (DIM == 3 ? (qz * BX * EX + qy * BX) * EP : qy * BX * EP) + qx * BX;
-      s_u[in == ~0ull || lane_in(in) ? cell0 + off : CS] = (double)x[q];
+      bool in;
+      if constexpr (W == 1) in = IN.m[q] == ~0ull || lane_in(IN.m[q]);
+      else in = qx * BX + G::lx(lane) < EX && qy * BX + G::ly(lane) < EX && (DIM == 2 || qz * BX + G::lz(lane) < SP::EZ);
+      s_u[in ? cell0 + off : CS] = (double)x[j];
     }
     __syncthreads();
-    for (int k = lane; k - lane < rg.y; k += 64) {
+    for (int k = 64 * wv + lane; k - lane < rg.y; k += 64 * W) {
       const int2 dc = dof;
       const int bc = ((DIM == 3 ? (code >> 8) * EX : 0) + ((code >> 4) & 15)) * EP + (code & 15);
       double v[2];
-      interp_pair<DIM, NP, EX, EP>(s_u + bc, t, v, [&] { rows(k + 64); });
+      interp_pair<DIM, NP, EX, EP>(s_u + bc, t, v, [&] { rows(k + 64 * W); });
       // keeps the sums out of the branches below (the compiler would sink
       // them there and hold every member in a register for them)
       asm volatile("" : "+v"(v[0]), "+v"(v[1]));
@@ -451,18 +473,19 @@ constexpr int kLapBlocksPerGroup = 4 * kLapBlocksPerWave;
 template <class TU, class TA, class TV, int DIM, bool ALL, bool DOT = false>
 __global__ __launch_bounds__(256) void k_lap(
     LRows lr, LPull lp, const QMeta* __restrict__ face, int nb, const TU* __restrict__ u,
-    const TA* __restrict__ a, TV* __restrict__ v, int64_t ld, int nrhs, double cd, double co,
+    const TA* __restrict__ a, TV* __restrict__ v, int64_t ld, int nrhs, int per, double cd, double co,
     const double* __restrict__ gsum, double gscale, int xcd, const double* __restrict__ coef,
     Skip skip, DotOut<TV> dot) {
   using G = Geo<DIM>;
   constexpr int BX = G::BX, KB = kLapBlocksPerWave;
   constexpr int step[3] = {1, BX, BX * BX};
   constexpr FaceLanes<DIM> FL = face_lanes<DIM>();
+  const int r0 = blockIdx.y * per, r1 = min(nrhs, r0 + per);
   if (ALL && (int)blockIdx.x < lr.groups) {   // BC entries: explicit rows only
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= lp.n_c) return;
     const int k = lp.bc[i];
-    for (int r = 0; r < nrhs; ++r)
+    for (int r = r0; r < r1; ++r)
       if (!skipped(skip, r, 0))
         v[r * ld + lp.n_s + i] = (TV)(k >= 0 ? pull_rows(lp, k, u + r * ld, co) : 0.0);
     return;
@@ -478,7 +501,7 @@ __global__ __launch_bounds__(256) void k_lap(
     int c[2 * DIM];
 #pragma unroll
     for (int f = 0; f < 2 * DIM; ++f) c[f] = id >= 0 ? lr.col[(int64_t)i * lr.nf + f] : -1;
-    for (int r = 0; r < nrhs; ++r) {
+    for (int r = r0; r < r1; ++r) {
       double d0 = 0.0, d1 = 0.0;
       if (id >= 0 && !skipped(skip, r, inst)) {
         double s = 0.0;
@@ -555,7 +578,7 @@ __global__ __launch_bounds__(256) void k_lap(
     }
   }
   const int zl = ((lane + step[DIM - 1]) & 63) << 2, zh = ((lane - step[DIM - 1]) & 63) << 2;
-  for (int r = 0; r < nrhs; ++r) {
+  for (int r = r0; r < r1; ++r) {
     if (skipped(skip, r, inst)) continue;
     // Every load of the wave's blocks first, then the exchanges and sums.
     // Every lane loads (its own or, absent, its block's first value where it
@@ -748,10 +771,7 @@ __device__ __forceinline__ void wave_sync() {
 // 403 now; sphere at h = 1/48, FP32, two right-hand sides: 319, 76 and 53.
 // Chunks of 16, 32 slots: 432, 414 us; 4, 8 steps at once: 414, 434.
 constexpr int kTSlots = 32, kTSteps = 4;
-// Two waves share a supertile where there are few: they halve its chain, but
-// fill and clear two cubes.  One wave, two: 28.6, 21.8 us at 0.1M DOFs (600
-// supertiles); 45.6, 41.7 at 2300; 60.6, 60.6 at 4500; 100, 109 at 9100.
-constexpr int kTSplitBelow = 4096;
+// Wavefronts of a supertile: kSplitBelow.
 template <class TS, int DIM, int W>
 __global__ __launch_bounds__(64 * W) void k_gather_T(EPull ep, SuperView sv,
                                                      const QMeta* __restrict__ meta,
@@ -1073,7 +1093,13 @@ static const Tune& tune_of(const cpm_band* b) {
 // What of a pass a launch does: all of it, or (measurement only) one part.
 enum { PART_ALL = 0, PART_MAIN = 1, PART_EXPLICIT = 2 };
 
-// a = E u for nrhs right-hand sides, in one launch.
+// Right-hand sides that a workgroup of the forward apply takes in turn.
+static int rhs_per_group(const cpm_band* b, int nrhs, const Skip& skip) {
+  const int fill = skip.f ? kMaxRhsGroups : kFillSupertiles / std::max(1, b->nst);
+  const int groups = std::max(1, std::min(nrhs, fill));
+  return (nrhs + groups - 1) / groups;
+}
+
 template <class T, int DIM>
 static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hipStream_t st,
                           int part, const Skip& skip) {
@@ -1084,13 +1110,15 @@ static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hi
   SuperView sv = sview(b);
   if (part == PART_MAIN) er.groups = 0;
   if (part == PART_EXPLICIT) sv.n = 0;
-  const int64_t g = (int64_t)er.groups + sv.n;
+  const int per = rhs_per_group(b, nrhs, skip);
+  const int waves = per > 1 || sv.n <= kSplitBelow ? 2 : 1;
+  const int64_t g = (int64_t)er.groups / waves + sv.n;
   if (!g) return;
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(64), 0, st, er, sv, b->st_meta, b->st_rng, u, a, b->n, nrhs, tn.xcd,
-                       skip);
+  auto multi = [&](auto pad, auto np) {
+    auto kern = waves == 2 ? k_gather<T, DIM, pad(), np(), 2> : k_gather<T, DIM, pad(), np(), 1>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)g, (nrhs + per - 1) / per), dim3(64 * waves), 0, st, er, sv, b->st_meta,
+                       b->st_rng, u, a, b->n, nrhs, per, tn.xcd, skip);
   };
-  auto multi = [&](auto pad, auto np) { go(k_gather<T, DIM, pad(), np()>); };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   using N3 = std::integral_constant<int, 3>;
@@ -1129,9 +1157,11 @@ static void launch_lap(const cpm_band* b, const Tune& tn, hipStream_t st, const 
   LPull lp{b->lt_pull, b->bc_lt, b->lt_start, b->lt_src, b->lrow_id, (int)b->n_s, (int)b->n_c};
   const int64_t g = (int64_t)lr.groups + (part == PART_EXPLICIT ? 0 : lap_groups(b));
   if (!g) return;
-  hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g), dim3(256), 0, st, lr, lp,
-                     b->blk_face, b->nb, u, a, v, ld, nrhs, cd, co, gsum, gscale, tn.xcd, coef,
-                     skip, dot);
+  // in a solver too: apart they read the blocks' masks each (203 against 196 ms)
+  const int per = rhs_per_group(b, nrhs, Skip{});
+  hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g, (nrhs + per - 1) / per),
+                     dim3(256), 0, st, lr, lp, b->blk_face, b->nb, u, a, v, ld, nrhs, per, cd, co,
+                     gsum, gscale, tn.xcd, coef, skip, dot);
   CPM_LAUNCH_CHECK();
 }
 
@@ -1262,7 +1292,7 @@ static void apply_T_dim(const cpm_band* b, double m, double n, int nrhs, const T
   const BcPull bc{b->bc_et, bc_groups(b), (int)b->n_s, (int)b->n_c};
   for (int r = 0; r < nrhs; r += t.nr) {
     const int k = std::min(t.nr, nrhs - r);
-    const int waves = (int64_t)b->nst * k <= kTSplitBelow ? 2 : 1;
+    const int waves = (int64_t)b->nst * k <= kSplitBelow ? 2 : 1;
     const int64_t g = (int64_t)ep.groups / waves + b->nst;
     auto kern = waves == 2 ? k_gather_T<T, DIM, 2> : k_gather_T<T, DIM, 1>;
     if (g)

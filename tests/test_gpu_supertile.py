@@ -61,6 +61,21 @@ def test_transpose_of_many_right_hand_sides_equals_one_at_a_time(kind, N, nrhs, 
         assert (z[k] - one).abs().max().item() <= tol * one.abs().max().item()
 
 
+@pytest.mark.parametrize("kind,N,p", [("circle", 40, 3), ("sphere", 24, 2), ("sphere", 72, 3)])
+@pytest.mark.parametrize("nrhs", [2, 7, 40])
+@pytest.mark.parametrize("dtype,tol", [("float64", 1e-12), ("float32", 2.4e-7)])
+def test_forward_of_many_right_hand_sides_equals_one_at_a_time(kind, N, p, nrhs, dtype, tol):
+    # columns apart, several to a workgroup with a shorter last group, in turn
+    import torch
+    from paper_2305_04711_amd import cpm
+    band = _band(kind, N, p)
+    u = _vec(band, nrhs, 4, dtype)
+    v = cpm.apply(band, u, 0.0, -1.0)
+    for k in range(nrhs):
+        one = cpm.apply(band, u[k].contiguous(), 0.0, -1.0)
+        assert (v[k] - one).abs().max().item() <= tol * one.abs().max().item()
+
+
 @pytest.mark.parametrize("N", [64, 112])
 def test_solve_residual_with_few_and_many_partial_sums(N):
     # at N = 112 the applies write more partials than one kernel adds by itself
