@@ -81,53 +81,78 @@ __device__ __forceinline__ double lanes_sum(double v) {
   return v;
 }
 
+// Orders a wavefront's LDS accesses among its lanes: the hardware takes them in
+// program order, so only the compiler is held back.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Explicit interpolation rows: a[id] = sum_o w_o u[col_o], 4^d lanes per row
 // (a wavefront in 3-D, a quarter of one in 2-D), lane = member; FP64 weights
 // and sums for both storage precisions.
+constexpr int kERowLds = 128;   // doubles of a wavefront
 struct ERows {
-  int n, groups;          // rows; workgroups that hold them (a multiple of 8)
+  int waves, groups;      // wavefronts of rows (ERowPack); those of the grid (a multiple of 8)
   const int* id;
   const int* col;
-  const double* w;
+  const double* w1;       // 1-D weights, 4 per axis
+  int p;
   const int* inst;        // composite: instance of each row
 };
-constexpr int kERowPasses = 4;   // row groups per wavefront whose loads go out together
-template <int DIM> constexpr int erows_per_group() {
-  return kERowPasses * (DIM == 3 ? 1 : 4);
-}
 
+// The wavefront's rows are bound by its vector-memory instructions, not by
+// bytes: with a load for each row's columns, member weights and number and a
+// store each, 1-D weights alone (96 bytes a row for 512) made them slower.
+// Four rows' columns now come in one load, their 1-D weights in another (s:
+// ERowPack::kRows * 4 * DIM doubles of the wavefront's own, the products formed
+// in registers) and the sums leave in one store.  Whole apply before and now:
+// sphere at h = 1/64 18.1, 17.4 us, 1/256, FP32, 142.7, 134.3 us; torus at
+// 1/512, FP64, 743, 731 us (the rows alone 39 and 25 us).
 template <class TS, int DIM>
 __device__ __forceinline__ void explicit_rows(const ERows& er, int wave, int lane,
                                               const TS* __restrict__ u, double* __restrict__ a,
-                                              int64_t ld, int r0, int r1, const Skip& skip) {
-  constexpr int M = DIM == 3 ? 64 : 16, RPW = 64 / M;
+                                              int64_t ld, int r0, int r1, const Skip& skip,
+                                              double* s) {
+  using EP = ERowPack<DIM>;
+  constexpr int M = EP::M, NW = EP::kRows * 4 * DIM;
+  if (wave >= er.waves) return;
   if (!er.inst && r1 == r0 + 1 && skipped(skip, r0, 0)) return;
-  const int o = lane & (M - 1);
-  int row[kERowPasses], c[kERowPasses];
-  double w[kERowPasses];
+  const int4 c4 = reinterpret_cast<const int4*>(er.col)[(int64_t)wave * 64 + lane];
+  const int c[4] = {c4.x, c4.y, c4.z, c4.w};
+  // lane j (2-D: of each 16) stores row j
+  const int j0 = lane & (M - 1);
+  const int64_t row = EP::row(wave, min(j0, 3), lane);
+  const int id = er.id[row], inst = er.inst ? er.inst[row] : 0;
+  double wl[(NW + 63) / 64];
 #pragma unroll
-  for (int j = 0; j < kERowPasses; ++j) {
-    const int i = (wave * kERowPasses + j) * RPW + lane / M;
-    row[j] = i < er.n ? i : -1;
-    const int64_t e = (int64_t)min(i, er.n - 1) * M + o;
-    c[j] = er.col[e];
-    w[j] = er.w[e];
-  }
+  for (int k = 0; k < (NW + 63) / 64; ++k)
+    wl[k] = er.w1[(int64_t)wave * NW + min(64 * k + lane, NW - 1)];
+#pragma unroll
+  for (int k = 0; k < (NW + 63) / 64; ++k) s[min(64 * k + lane, NW - 1)] = wl[k];
+  wave_sync();
+  const int mo = erow_member<DIM>(er.p, j0);
+  double w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) w[j] = erow_weight<DIM>(s + EP::row(0, j, lane) * 4 * DIM, mo);
   for (int r = r0; r < r1; ++r) {
     // every lane loads (an absent member's lane entry 0, which it drops), so
     // that no load waits behind a branch for the one before it
-    double v[kERowPasses];
+    double v[4], out = 0.0;
 #pragma unroll
-    for (int j = 0; j < kERowPasses; ++j) v[j] = (double)u[r * ld + max(c[j], 0)];
+    for (int j = 0; j < 4; ++j) v[j] = (double)u[r * ld + max(c[j], 0)];
 #pragma unroll
-    for (int j = 0; j < kERowPasses; ++j) v[j] = c[j] >= 0 ? w[j] * v[j] : 0.0;
+    for (int j = 0; j < 4; ++j) v[j] = lanes_sum<M>(c[j] >= 0 ? w[j] * v[j] : 0.0);
 #pragma unroll
-    for (int j = 0; j < kERowPasses; ++j) {
-      const double s = lanes_sum<M>(v[j]);
-      if (row[j] < 0 || o != M - 1) continue;
-      if (skipped(skip, r, er.inst ? er.inst[row[j]] : 0)) continue;
-      a[r * ld + er.id[row[j]]] = s;
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (DIM == 3) {
+        const long long b = __double_as_longlong(v[j]);
+        v[j] = __longlong_as_double(((long long)lane_i32((int)(b >> 32), 63) << 32) |
+                                    (unsigned)lane_i32((int)(unsigned)(b & 0xffffffffll), 63));
+      }
+      out = j0 == j ? v[j] : out;
     }
+    if (j0 < 4 && id >= 0 && !skipped(skip, r, inst)) a[r * ld + id] = out;
   }
 }
 
@@ -252,6 +277,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ?
   constexpr int EX = SP::EX, EP = EX + PAD, BX = G::BX, NB = SP::NB;
   constexpr InsideMasks<DIM> IN = inside_masks<DIM>();
   constexpr int CS = SP::EZ * EX * EP;
+  static_assert(CS >= W * kERowLds, "explicit rows' weights");
   __shared__ double s_u[CS + 1];
   constexpr int NQ = (NB + W - 1) / W;   // blocks staged by a wave
   const int lane = threadIdx.x & 63;
@@ -261,7 +287,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ?
   if (g >= sv.n) {
     g -= sv.n;
     if (xcd) g = xcd_remap(g, er.groups / W);
-    explicit_rows<TS, DIM>(er, g * W + wv, lane, u, a, ld, r0, r1, skip);
+    explicit_rows<TS, DIM>(er, g * W + wv, lane, u, a, ld, r0, r1, skip, s_u + wv * kERowLds);
     return;
   }
   if (xcd) g = xcd_remap(g, sv.n);
@@ -738,13 +764,6 @@ __device__ __forceinline__ void explicit_targets(const EPull& ep, int wave, int 
   }
 }
 
-// Orders a wavefront's LDS accesses among its lanes: the hardware takes them in
-// program order, so only the compiler is held back.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // E^T c of the tile rows, a workgroup of W wavefronts per supertile.  The rows
 // of one stencil base add w c into the same 4^d members, a small matrix
 // product summed over the rows: in 3-D G[z][y][x] += sum_i (c_i wz_i[z]
@@ -1104,9 +1123,8 @@ template <class T, int DIM>
 static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hipStream_t st,
                           int part, const Skip& skip) {
   const Tune& tn = tune_of<T>(b);
-  constexpr int RG = erows_per_group<DIM>();
-  ERows er{b->n_erows, (int)(((int64_t)b->n_erows + 8 * RG - 1) / (8 * RG)) * 8, b->erow_id,
-           b->ecol, b->ew, b->erow_inst};
+  const int ew = ERowPack<DIM>::padded(b->n_erows) / ERowPack<DIM>::kRows;
+  ERows er{ew, (ew + 7) / 8 * 8, b->erow_id, b->ecol4, b->ew1, b->p, b->erow_inst};
   SuperView sv = sview(b);
   if (part == PART_MAIN) er.groups = 0;
   if (part == PART_EXPLICIT) sv.n = 0;

@@ -426,7 +426,7 @@ void build_composite(cpm_batch* B, hipStream_t st) {
     nb += up(b->nb, kBlkPad);
     nt += b->nst;
     ns += b->n_slots;
-    ne += b->n_erows;
+    ne += erow_padded(c->dim, b->n_erows);
     nl += up(b->n_lrows, kRowPad);
   }
   B->total = B->D[ni];
@@ -446,8 +446,8 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   c->slot_frac64 = c->alloc<double2>((size_t)d * ns);
   c->slot_frac32 = c->alloc<float2>((size_t)d * ns);
   c->erow_id = c->alloc<int>(ne);
-  c->ecol = c->alloc<int>((size_t)ne * nm);
-  c->ew = c->alloc<double>((size_t)ne * nm);
+  c->ecol4 = c->alloc<int>((size_t)ne * nm);
+  c->ew1 = c->alloc<double>((size_t)ne * 4 * d);
   c->lrow_id = c->alloc<int>(nl);
   c->lcol = c->alloc<int>((size_t)nl * nf);
   c->lrow_inst = c->alloc<int>(nl);
@@ -479,11 +479,12 @@ void build_composite(cpm_batch* B, hipStream_t st) {
     }
     CPM_HIP(hipMemcpyAsync(c->slot_base + os, b->slot_base, sizeof(unsigned short) * b->n_slots,
                            hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_cat_int, g(b->n_erows), dim3(256), 0, st, b->erow_id, c->erow_id + oe,
-                       (int64_t)b->n_erows, add);
-    hipLaunchKernelGGL(k_cat_int, g((int64_t)b->n_erows * nm), dim3(256), 0, st, b->ecol,
-                       c->ecol + oe * nm, (int64_t)b->n_erows * nm, add);
-    CPM_HIP(hipMemcpyAsync(c->ew + oe * nm, b->ew, sizeof(double) * b->n_erows * nm,
+    const int nep = erow_padded(d, b->n_erows);   // whole wavefronts of rows
+    hipLaunchKernelGGL(k_cat_int, g(nep), dim3(256), 0, st, b->erow_id, c->erow_id + oe,
+                       (int64_t)nep, add);
+    hipLaunchKernelGGL(k_cat_int, g((int64_t)nep * nm), dim3(256), 0, st, b->ecol4,
+                       c->ecol4 + oe * nm, (int64_t)nep * nm, add);
+    CPM_HIP(hipMemcpyAsync(c->ew1 + oe * 4 * d, b->ew1, sizeof(double) * nep * 4 * d,
                            hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_cat_int, g(b->n_lrows), dim3(256), 0, st, b->lrow_id, c->lrow_id + ol,
                        (int64_t)b->n_lrows, add);
@@ -491,15 +492,14 @@ void build_composite(cpm_batch* B, hipStream_t st) {
                        c->lcol + ol * nf, (int64_t)b->n_lrows * nf, add);
     hipLaunchKernelGGL(k_fill_int, g(b->n_lrows), dim3(256), 0, st, c->lrow_inst + ol,
                        (int64_t)b->n_lrows, i);
-    hipLaunchKernelGGL(k_fill_int, g(b->n_erows), dim3(256), 0, st, c->erow_inst + oe,
-                       (int64_t)b->n_erows, i);
+    hipLaunchKernelGGL(k_fill_int, g(nep), dim3(256), 0, st, c->erow_inst + oe, (int64_t)nep, i);
     CPM_LAUNCH_CHECK();
     B->h_boff[i] = (int)(ob / kBlkPad);
     B->h_loff[i] = (int)(ol / kRowPad);
     ob += up(b->nb, kBlkPad);
     ot += b->nst;
     os += b->n_slots;
-    oe += b->n_erows;
+    oe += nep;
     ol += up(b->n_lrows, kRowPad);
   }
   std::vector<double> coef(2 * ni);

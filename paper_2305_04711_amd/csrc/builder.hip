@@ -631,7 +631,7 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
                                                   const double* cp, const int* row_c,
                                                   const int* alpha_of, const double* side_v,
                                                   const int* eflag, const int* eidx,
-                                                  int* erow_id, int* ecol, double* ew,
+                                                  int* erow_id, int* ecol, double* ew1,
                                                   int* ebase) {
   NODE_PROLOGUE(DIM);
   constexpr int NM = DIM == 3 ? 64 : 16;
@@ -643,8 +643,11 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
   double t[3];
   stencil_base<DIM>(y, N, B.p, base, t);
   for (int a = 0; a < DIM; ++a) ebase[r * DIM + a] = base[a];
-  double w[3][4];
-  for (int a = 0; a < DIM; ++a) lagrange_p<double>(B.p, t[a], w[a]);
+  double w[4];
+  for (int a = 0; a < DIM; ++a) {
+    lagrange_p<double>(B.p, t[a], w);
+    for (int o = 0; o < 4; ++o) ew1[((int64_t)r * DIM + a) * 4 + o] = w[o];
+  }
   const int bb = block_of<DIM>(B, base[0], base[1], base[2]);
   const int lx = base[0] & (G::BX - 1), ly = base[1] & (G::BX - 1),
             lz = DIM == 3 ? (base[2] & (G::BX - 1)) : 0;
@@ -654,7 +657,6 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
   for (int o = 0; o < NM; ++o) {
     if (o >= nmp) {   // quadratic stencils fill the first (p+1)^d slots
       ecol[(int64_t)r * NM + o] = -1;
-      ew[(int64_t)r * NM + o] = 0.0;
       continue;
     }
     const int a = o % np, b = (o / np) % np, c = o / (np * np);
@@ -662,9 +664,7 @@ __global__ __launch_bounds__(256) void k_erow_pde(Blocks B, int nb, int N, int64
     if (row_c[j] == rc && alpha_of[j] >= 0 &&
         dot3<DIM>(vi, load_v(side_v, n_s, j, DIM)) < 0.0)
       j = alpha_of[j];
-    const double wt = DIM == 3 ? (w[2][c] * w[1][b]) * w[0][a] : w[1][b] * w[0][a];
     ecol[(int64_t)r * NM + o] = j;
-    ew[(int64_t)r * NM + o] = wt;
   }
 }
 
@@ -685,7 +685,7 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
                           cpm_surface S, IBCList L, const int* bc_node, const double* bc_cpc,
                           const int* bc_side, const int* bc_curve, const int* bc_k,
                           const int* row_c, const int* alpha_of, const double* side_v, int r0,
-                          int* erow_id, int* ecol, double* ew, int* ebase,
+                          int* erow_id, int* ecol, double* ew1, int* ebase,
                           double* ecoef, unsigned long long* counters) {
   using G = Geo<DIM>;
   constexpr int NM = DIM == 3 ? 64 : 16;
@@ -697,10 +697,8 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
   const bool neumann = L.c[bc_curve[k]].bc[served > 0 ? 0 : 1] == CPM_BC_NEUMANN;
   ecoef[k] = neumann ? 0.0 : (order == 2 ? 2.0 : 1.0);
   if (order != 2 && !neumann) {
-    for (int o = 0; o < NM; ++o) {
-      ecol[(int64_t)r * NM + o] = -1;
-      ew[(int64_t)r * NM + o] = 0.0;
-    }
+    for (int o = 0; o < NM; ++o) ecol[(int64_t)r * NM + o] = -1;
+    for (int o = 0; o < 4 * DIM; ++o) ew1[(int64_t)r * DIM * 4 + o] = 0.0;
     for (int a = 0; a < DIM; ++a) ebase[r * DIM + a] = 0;
     return;
   }
@@ -714,8 +712,12 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
   double t[3];
   stencil_base<DIM>(y, N, B.p, base, t);
   for (int a = 0; a < DIM; ++a) ebase[r * DIM + a] = base[a];
-  double w[3][4];
-  for (int a = 0; a < DIM; ++a) lagrange_p<double>(B.p, t[a], w[a]);
+  double w[4];
+  for (int a = 0; a < DIM; ++a) {   // the row's sign goes with the last axis
+    lagrange_p<double>(B.p, t[a], w);
+    for (int o = 0; o < 4; ++o)
+      ew1[((int64_t)r * DIM + a) * 4 + o] = a == DIM - 1 ? sgn * w[o] : w[o];
+  }
   const int bb = block_of<DIM>(B, base[0], base[1], base[2]);
   const int lx = base[0] & (G::BX - 1), ly = base[1] & (G::BX - 1),
             lz = DIM == 3 ? (base[2] & (G::BX - 1)) : 0;
@@ -726,7 +728,6 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
   for (int o = 0; o < NM; ++o) {
     if (o >= nmp) {
       ecol[(int64_t)r * NM + o] = -1;
-      ew[(int64_t)r * NM + o] = 0.0;
       continue;
     }
     const int a = o % np, b = (o / np) % np, c = o / (np * np);
@@ -737,9 +738,7 @@ __global__ void k_erow_bc(Blocks B, int N, int64_t n_s, int64_t n_c, int order,
                !(dot3<DIM>(vj, load_v(side_v, n_s, m, DIM)) < 0.0)) {
       m = alpha_of[m];
     }
-    const double wt = sgn * (DIM == 3 ? (w[2][c] * w[1][b]) * w[0][a] : w[1][b] * w[0][a]);
     ecol[(int64_t)r * NM + o] = m;
-    ew[(int64_t)r * NM + o] = wt;
   }
   if (holes) atomicAdd(&counters[3], (unsigned long long)holes);
 }
@@ -988,13 +987,26 @@ __global__ void k_pull_pairs_l(int nrows, int nf, int64_t n_s, const int* row_id
 }
 
 // E pull entries in sorted order: the source's weight and its row's DOF, which replaces the source index in place
-__global__ void k_pull_denorm_e(int total, int* src, int nm, const int* erow_id, const double* ew,
+template <int DIM>
+__global__ void k_pull_denorm_e(int total, int* src, int p, const int* erow_id, const double* ew1,
                                 double* w64) {
+  constexpr int NM = DIM == 3 ? 64 : 16;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int g = src[e];
-  w64[e] = ew[g];
-  src[e] = erow_id[g / nm];
+  w64[e] = erow_weight<DIM>(ew1 + (int64_t)(g / NM) * 4 * DIM, erow_member<DIM>(p, g % NM));
+  src[e] = erow_id[g / NM];
+}
+
+// The explicit rows' columns as the apply loads them (ERowPack), no column in
+// the rows that fill the last wavefront up.
+template <int DIM>
+__global__ void k_erow_pack(int n, int np, const int* ecol, int* ecol4) {
+  using EP = ERowPack<DIM>;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (int64_t)np * EP::M) return;
+  const int64_t row = EP::row(t >> 8, (int)(t & 3), (int)(t >> 2) & 63);
+  ecol4[t] = row < n ? ecol[row * EP::M + ((t >> 2) & (EP::M - 1))] : -1;
 }
 
 // Sorts the pairs by target (stable: sources ascending within a target) and
@@ -1350,13 +1362,19 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
     Tmp<int> eidx(b, n_s);
     const int64_t ne_pde = scan_exclusive_i32(eflag.p, eidx.p, n_s, st, b->da);
     b->n_erows = (int)(ne_pde + n_c);
-    b->erow_id = b->alloc<int>(b->n_erows);
+    const int np = ERowPack<DIM>::padded(b->n_erows);
+    b->erow_id = b->alloc<int>(np);
     b->ecol = b->alloc<int>((size_t)b->n_erows * NM);
-    b->ew = b->alloc<double>((size_t)b->n_erows * NM);
+    b->ecol4 = b->alloc<int>((size_t)np * NM);
+    b->ew1 = b->alloc<double>((size_t)np * 4 * DIM);
+    if (np) {
+      CPM_HIP(hipMemsetAsync(b->erow_id, 0xff, sizeof(int) * np, st));
+      CPM_HIP(hipMemsetAsync(b->ew1, 0, sizeof(double) * np * 4 * DIM, st));
+    }
     b->ebase = b->alloc<int>((size_t)b->n_erows * DIM);
     if (ne_pde)
       hipLaunchKernelGGL(k_erow_pde<DIM>, gnode, dim3(256), 0, st, B, nb, N, n_s, b->cp, row_c.p,
-                         alpha_of.p, side_v.p, eflag.p, eidx.p, b->erow_id, b->ecol, b->ew,
+                         alpha_of.p, side_v.p, eflag.p, eidx.p, b->erow_id, b->ecol, b->ew1,
                          b->ebase);
     CPM_LAUNCH_CHECK();
     b->bc_ecoef = b->alloc<double>(n_c);
@@ -1364,7 +1382,10 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       hipLaunchKernelGGL(k_erow_bc<DIM>, dim3(grid_for(n_c, 128)), dim3(128), 0, st, B, N, n_s,
                          n_c, b->order, S, L, b->bc_node, b->bc_cpc, b->bc_side, b->bc_curve,
                          bc_kp->p, row_c.p, alpha_of.p, side_v.p, (int)ne_pde, b->erow_id,
-                         b->ecol, b->ew, b->ebase, b->bc_ecoef, counters.p);
+                         b->ecol, b->ew1, b->ebase, b->bc_ecoef, counters.p);
+    if (np)
+      hipLaunchKernelGGL(k_erow_pack<DIM>, dim3(grid_for((int64_t)np * NM, 256)), dim3(256), 0, st,
+                         b->n_erows, np, b->ecol, b->ecol4);
     CPM_LAUNCH_CHECK();
     unsigned long long hc[4];
     CPM_HIP(hipMemcpyAsync(hc, counters.p, sizeof(hc), hipMemcpyDeviceToHost, st));
@@ -1482,8 +1503,8 @@ void build(cpm_band* b, hipStream_t st, const Filter& F) {
       CPM_HIP(hipStreamSynchronize(st));
       b->n_et_entries = total;
       b->et_w = b->alloc<double>(total);
-      hipLaunchKernelGGL(k_pull_denorm_e, dim3(grid_for(total, 256)), dim3(256), 0, st, total,
-                         b->et_src, NM, b->erow_id, b->ew, b->et_w);
+      hipLaunchKernelGGL(k_pull_denorm_e<DIM>, dim3(grid_for(total, 256)), dim3(256), 0, st, total,
+                         b->et_src, b->p, b->erow_id, b->ew1, b->et_w);
       CPM_LAUNCH_CHECK();
     }
     const int64_t nl = (int64_t)b->n_lrows * 2 * DIM * 2;

@@ -99,6 +99,21 @@ struct QMeta {
   int pad;
 };
 
+// Explicit E rows as a wavefront takes them: kRows rows, four to a lane (M
+// lanes to a row, lane = member).  Row j of lane l is
+// row(wavefront, j, l); its column is component j of the lane's int4.
+template <int DIM> struct ERowPack {
+  static constexpr int M = DIM == 3 ? 64 : 16, kRows = 4 * (64 / M);
+  __host__ __device__ static int64_t row(int64_t wave, int j, int lane) {
+    return (wave * 4 + j) * (64 / M) + lane / M;
+  }
+  static int padded(int n) { return (n + kRows - 1) / kRows * kRows; }
+};
+inline int erow_padded(int dim, int n) {
+  return dim == 3 ? ERowPack<3>::padded(n) : ERowPack<2>::padded(n);
+}
+
+
 // The slots of a block (mask) that have an entry in some buffer, one after
 // the other from off.
 struct Pull {
@@ -215,9 +230,11 @@ struct cpm_band {
 
   // rows with explicit interpolation stencils (swapped PDE rows, BC rows)
   int n_erows = 0;
-  int* erow_id = nullptr;             // [n_erows]
+  int* erow_id = nullptr;             // [padded n_erows], -1 past the last
   int* ecol = nullptr;                // [n_erows][4^dim]
-  double* ew = nullptr;               // [n_erows][4^dim]
+  int* ecol4 = nullptr;               // [padded n_erows][4^dim]: ecol as the apply loads it (ERowPack)
+  double* ew1 = nullptr;              // [padded n_erows][dim][4]: 1-D weights, the row's sign with
+                                      // the last axis
   int* ebase = nullptr;               // [n_erows][dim]
 
   // rows with explicit FD stencils (swapped PDE rows, BC rows)

@@ -41,4 +41,20 @@ __device__ __forceinline__ void lagrange_p(int p, T t, T w[4]) {
   else lagrange3<T>(t, w);
 }
 
+// An explicit row's weights are products of 1-D weights w1[axis][4].  Member o
+// of a row (x fastest, (p + 1)^d members) as its place per axis, 4 bits each;
+// places past the row's stay in range.
+template <int DIM>
+__device__ __forceinline__ int erow_member(int p, int o) {
+  const int np = p + 1, b = o / np;
+  const int y = DIM == 3 ? b % np : min(b, 3), z = DIM == 3 ? min(b / np, 3) : 0;
+  return (o - b * np) | y << 4 | z << 8;
+}
+
+template <int DIM>
+__device__ __forceinline__ double erow_weight(const double* __restrict__ w1, int m) {
+  const double y = w1[4 + ((m >> 4) & 15)];
+  return DIM == 3 ? (w1[8 + (m >> 8)] * y) * w1[m & 15] : y * w1[m & 15];
+}
+
 }  // namespace cpm
