@@ -1013,30 +1013,43 @@ __global__ __launch_bounds__(256) void k_combine(BcPull bc, const QMeta* __restr
     auto from = [&](int j, int q) {
       return ((long long)lane_i32(pm.w, 16 * j + q) << 32) | (unsigned)lane_i32(pm.z, 16 * j + q);
     };
-    double s[KB][NP + 1];
-    TS wl[KB], yl[KB];
-    int own[KB];
-    // every load first (a lane without an entry loads its block's first)
+    // Loads for the longer of the blocks' lists of supertiles, two, four or
+    // all 2^d long (the rest are empty): a wave is bound by its accesses to
+    // memory.  Whole transpose, torus at h = 1/256: 398 us with 2^d always, 380.
+    const unsigned long long some = __ballot(e < NP && (pm.x | pm.y) != 0);
+    int longest = 0;
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      own[j] = lane_i32(pm.z, 16 * j + 15) + (int)lane_rank(mask(j, 15));
-      wl[j] = w[own[j]];
-      if (DOT) yl[j] = dot.y[own[j]];
+    for (int j = 0; j < KB; ++j) longest = max(longest, __popcll((some >> (16 * j)) & 0xffffull));
+    auto take = [&](auto nq) {
+      constexpr int NQ = nq();
+      double s[KB][NQ + 1];
+      TS wl[KB], yl[KB];
+      int own[KB];
+      // every load first (a lane without an entry loads its block's first)
 #pragma unroll
-      for (int q = 0; q < NP; ++q) s[j][q] = (buf + from(j, q))[lane_rank(mask(j, q))];
-      s[j][NP] = mask(j, 8) ? (x + from(j, 8))[lane_rank(mask(j, 8))] : 0.0;
-    }
+      for (int j = 0; j < KB; ++j) {
+        own[j] = lane_i32(pm.z, 16 * j + 15) + (int)lane_rank(mask(j, 15));
+        wl[j] = w[own[j]];
+        if (DOT) yl[j] = dot.y[own[j]];
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      double ev = 0.0;
-#pragma unroll
-      for (int q = 0; q <= NP; ++q) {
-        asm volatile("" : "+v"(s[j][q]));   // the loads stay above
-        ev += lane_in(mask(j, q < NP ? q : 8)) ? s[j][q] : 0.0;
+        for (int q = 0; q < NQ; ++q) s[j][q] = (buf + from(j, q))[lane_rank(mask(j, q))];
+        s[j][NQ] = mask(j, 8) ? (x + from(j, 8))[lane_rank(mask(j, 8))] : 0.0;
       }
-      if (blk0 + j < nb && lane_in(mask(j, 15)))
-        put(own[j], (double)wl[j], ev, DOT ? (double)yl[j] : 0.0);
-    }
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        double ev = 0.0;
+#pragma unroll
+        for (int q = 0; q <= NQ; ++q) {
+          asm volatile("" : "+v"(s[j][q]));   // the loads stay above
+          ev += lane_in(mask(j, q < NQ ? q : 8)) ? s[j][q] : 0.0;
+        }
+        if (blk0 + j < nb && lane_in(mask(j, 15)))
+          put(own[j], (double)wl[j], ev, DOT ? (double)yl[j] : 0.0);
+      }
+    };
+    if (longest <= 2) take(std::integral_constant<int, 2>{});
+    else if (DIM == 2 || longest <= 4) take(std::integral_constant<int, 4>{});
+    else take(std::integral_constant<int, NP>{});
   }
   if constexpr (DOT) group_dot2(d0, d1, dot.part, dot.np, part);
 }

@@ -554,14 +554,13 @@ __global__ void k_st_of_blk(int nb, const int* sid_ex, const int* head, const in
 }
 
 // Per block, the supertiles whose cubes reach it and where its nodes' sums
-// lie in the buffer (entries 0 .. 2^d - 1, in a fixed order).
+// lie in the buffer (entries 0 .. 2^d - 1, in a fixed order, empty ones last).
 template <int DIM>
 __global__ void k_st_pull(Blocks B, int nb, const int* st_of_blk, const QMeta* meta, Pull* pull) {
   using SP = Super<DIM>;
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int i = (int)(g >> 3), k = (int)(g & 7);
-  if (i >= nb) return;
-  const int4 c = B.coord[i];
+  const int4 c = B.coord[min(i, nb - 1)];
   // along x and y a block is the first (even), second (odd) or third (even)
   // of a cube's three; along z the first or second of two
   const int kx = k & 1, ky = (k >> 1) & 1, kz = k >> 2;
@@ -583,7 +582,11 @@ __global__ void k_st_pull(Blocks B, int nb, const int* st_of_blk, const QMeta* m
       out.mask = m[q].mask & SP::inside(q);
     }
   }
-  pull[(int64_t)i * 9 + k] = out;
+  // eight lanes to a block
+  const unsigned some = (unsigned)(__ballot(out.mask != 0ull) >> (threadIdx.x & 56)) & 0xffu;
+  const unsigned below = (1u << k) - 1u;
+  const int at = out.mask ? __popc(some & below) : __popc(some) + __popc(~some & below);
+  if (i < nb) pull[(int64_t)i * 9 + at] = out;
 }
 
 __device__ __forceinline__ int lower_bound_i32(const int* a, int n, int key) {
