@@ -60,10 +60,13 @@ __device__ __forceinline__ void set_scal(Scal* S, const Scal& q) {
 // 74.4 with up to 4096 workgroups of one element a thread).
 constexpr int kRedThreads = 256;
 constexpr int kMaxParts = 1024;
-// Partials that every workgroup of a consumer adds up by itself; more are
-// added by k_parts to kFoldParts first.  A sum over 2048 pairs reads 32 KB
-// from the L2 in about 2 us, less than another launch (5 us).
-constexpr int kDirectParts = 2048;
+// Partials that every workgroup of a consumer adds up by itself, kPartLoads
+// loads of a thread at once (one at a time: 60.3 us an iteration at 0.44M DOFs
+// and 1400 partials, 58.8 now); more are added by k_parts to kFoldParts first.
+// At 2900 partials an iteration takes 113.8 us without k_parts and 118.2 with
+// it; from 4096 on each workgroup would read more than 64 KB.
+constexpr int kDirectParts = 4096;
+constexpr int kPartLoads = 8;
 constexpr int kFoldParts = 256;
 
 static int red_grid(int64_t n) {
@@ -101,9 +104,20 @@ __device__ __forceinline__ void put_parts(double v[2], double* part, int ld) {
 __device__ __forceinline__ void add_parts(const double* __restrict__ part, int ld, int np,
                                           double v[2]) {
   v[0] = v[1] = 0.0;
-  for (int i = threadIdx.x; i < np; i += kRedThreads) {
-    v[0] += part[i];
-    v[1] += part[ld + i];
+  for (int i0 = threadIdx.x; i0 < np; i0 += kPartLoads * kRedThreads) {
+    double a[kPartLoads], b[kPartLoads];
+#pragma unroll
+    for (int j = 0; j < kPartLoads; ++j) {
+      const int i = min(i0 + j * kRedThreads, np - 1);
+      a[j] = part[i];
+      b[j] = part[ld + i];
+    }
+#pragma unroll
+    for (int j = 0; j < kPartLoads; ++j) {
+      const bool in = i0 + j * kRedThreads < np;
+      v[0] += in ? a[j] : 0.0;
+      v[1] += in ? b[j] : 0.0;
+    }
   }
   wg_sum2(v);
 }

@@ -76,9 +76,10 @@ def test_forward_of_many_right_hand_sides_equals_one_at_a_time(kind, N, p, nrhs,
         assert (v[k] - one).abs().max().item() <= tol * one.abs().max().item()
 
 
-@pytest.mark.parametrize("N", [64, 112])
+@pytest.mark.parametrize("N", [64, 112, 136])
 def test_solve_residual_with_few_and_many_partial_sums(N):
-    # at N = 112 the applies write more partials than one kernel adds by itself
+    # 1400, 4000 and 6000 partials of an apply: in one and two passes of a
+    # thread's loads, and folded by a kernel of their own first
     import torch
     from paper_2305_04711_amd import cpm
     band = _band("sphere", N)
