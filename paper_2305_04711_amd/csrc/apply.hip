@@ -190,12 +190,14 @@ template <> __device__ __forceinline__ double frac_row<float>(const SuperView& s
   return (double)reinterpret_cast<const float*>(sv.frac32 + s0)[i];
 }
 
-// Interpolation of the two rows of a slot from the staged cube (sum-factorised
-// tensor product): x lines first, then y, then z; FP64 arithmetic.  NP = p + 1
-// stencil nodes per axis.  Both rows read the same members, each once.
-template <int DIM, int NP, int E, int EP, class NEXT>
-__device__ __forceinline__ void interp_pair(const double* __restrict__ s, const double2 t[DIM],
-                                            double out[2], NEXT next) {
+// Interpolation of the two rows of a slot from the staged cubes, one of each
+// right-hand side that is on (sum-factorised tensor product): x lines first,
+// then y, then z; FP64 arithmetic.  NP = p + 1 stencil nodes per axis.  Both
+// rows read the same members, each once.
+template <int DIM, int NP, int E, int EP, int NR, class NEXT, class PUT>
+__device__ __forceinline__ void interp_pair(const double* __restrict__ s0, int cube,
+                                            const bool on[NR], const double2 t[DIM], NEXT next,
+                                            PUT put) {
   double wx[2][4], wy[2][4], wz[2][4];
   constexpr int P = NP - 1;
   lagrange_p<double>(P, t[0].x, wx[0]);
@@ -213,23 +215,32 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s, const 
     lagrange_p<double>(P, tz.x, wz[0]);
     lagrange_p<double>(P, tz.y, wz[1]);
   }
-  out[0] = out[1] = 0.0;
 #pragma unroll
-  for (int c = 0; c < (DIM == 3 ? NP : 1); ++c) {
-    double acc[2] = {0.0, 0.0};
+  for (int i = 0; i < NR; ++i) {
+    if (!on[i]) continue;
+    const double* s = s0 + i * cube;
+    double out[2] = {0.0, 0.0};
 #pragma unroll
-    for (int b = 0; b < NP; ++b) {
-      const double* row = s + (c * E + b) * EP;
-      const double r0 = row[0], r1 = row[1], r2 = row[2], r3 = NP == 4 ? row[3] : 0.0;
+    for (int c = 0; c < (DIM == 3 ? NP : 1); ++c) {
+      double acc[2] = {0.0, 0.0};
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        double x = wx[k][0] * r0 + wx[k][1] * r1 + wx[k][2] * r2;
-        if (NP == 4) x += wx[k][3] * r3;
-        acc[k] += wy[k][b] * x;
+      for (int b = 0; b < NP; ++b) {
+        const double* row = s + (c * E + b) * EP;
+        const double r0 = row[0], r1 = row[1], r2 = row[2], r3 = NP == 4 ? row[3] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          double x = wx[k][0] * r0 + wx[k][1] * r1 + wx[k][2] * r2;
+          if (NP == 4) x += wx[k][3] * r3;
+          acc[k] += wy[k][b] * x;
+        }
       }
-    }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) out[k] = DIM == 3 ? out[k] + wz[k][c] * acc[k] : acc[k];
+      for (int k = 0; k < 2; ++k) out[k] = DIM == 3 ? out[k] + wz[k][c] * acc[k] : acc[k];
+    }
+    // keeps the sums out of the branches that store them (the compiler would
+    // sink them there and hold every member in a register for them)
+    asm volatile("" : "+v"(out[0]), "+v"(out[1]));
+    put(i, out);
   }
 }
 
@@ -267,8 +278,18 @@ constexpr int kSplitBelow = 4096;
 // 2000), and in pass 1 of a solver, whose systems end at different times
 // (batched solve of 18 systems: 220 and 195 ms).
 constexpr int kFillSupertiles = 2048, kMaxRhsGroups = 4096;
-template <class TS, int DIM, int PAD, int NP, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ? 4 : 5))) void k_gather(
+// A workgroup with several right-hand sides takes two at a time (NR), a cube
+// each, so that a slot's data and weights are read and formed once for both:
+// two, three and eight columns 203, 302, 795 us with one at a time, 178, 282,
+// 728 now (torus at h = 1/192, FP64).
+// Wavefronts per SIMD to fit the registers to: five where that spills nothing
+// (FP64 pairs at five spill 6 registers: 198, 306, 766 us).
+constexpr int gather_waves(int size, int w, int nr) {
+  return nr == 2 ? (size == 8 ? 4 : 5) : w == 2 ? 5 : 4;
+}
+template <class TS, int DIM, int PAD, int NP, int W, int NR>
+__global__ __launch_bounds__(64 * W) __attribute__((
+    amdgpu_waves_per_eu(gather_waves(sizeof(TS), W, NR)))) void k_gather(
     ERows er, SuperView sv, const QMeta* __restrict__ meta, const int4* __restrict__ rng,
     const TS* __restrict__ u, double* __restrict__ a, int64_t ld, int nrhs, int per, int xcd,
     Skip skip) {
@@ -278,7 +299,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ?
   constexpr InsideMasks<DIM> IN = inside_masks<DIM>();
   constexpr int CS = SP::EZ * EX * EP;
   static_assert(CS >= W * kERowLds, "explicit rows' weights");
-  __shared__ double s_u[CS + 1];
+  __shared__ double s_u[NR][CS + 1];
   constexpr int NQ = (NB + W - 1) / W;   // blocks staged by a wave
   const int lane = threadIdx.x & 63;
   const int wv = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -287,7 +308,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ?
   if (g >= sv.n) {
     g -= sv.n;
     if (xcd) g = xcd_remap(g, er.groups / W);
-    explicit_rows<TS, DIM>(er, g * W + wv, lane, u, a, ld, r0, r1, skip, s_u + wv * kERowLds);
+    explicit_rows<TS, DIM>(er, g * W + wv, lane, u, a, ld, r0, r1, skip, s_u[0] + wv * kERowLds);
     return;
   }
   if (xcd) g = xcd_remap(g, sv.n);
@@ -310,47 +331,64 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ?
   };
   int cell0 = DIM == 3 ? (G::lz(lane) * EX + G::ly(lane)) * EP + G::lx(lane)
                        : G::ly(lane) * EP + G::lx(lane);
-  for (int r = r0; r < r1; ++r) {
+  for (int r = r0; r < r1; r += NR) {
     // keeps the cells of all staged blocks from living in registers throughout
     asm volatile("" : "+v"(cell0));
-    if (skipped(skip, r, rg.z)) continue;
+    bool on[NR];
+    if constexpr (NR == 1) {
+      if (skipped(skip, r, rg.z)) continue;
+      on[0] = true;
+    } else {
+      bool any = false;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        on[i] = r + i < r1 && !skipped(skip, r + i, rg.z);
+        any |= on[i];
+      }
+      if (!any) continue;
+    }
     // the first pass's row data is requested before the staging loads
     rows(64 * wv + lane);
-    __syncthreads();   // the previous right-hand side's rows are done
-    // Every lane loads (an absent node's lane the block's first value, which
-    // it drops): under a condition each load would be a basic block of its
-    // own and wait for the one before it.
-    // Cells of absent nodes hold that value: no tile row's stencil has one.
-    const TS* ur = u + r * ld;
-    TS x[NQ];
+    __syncthreads();   // the previous right-hand sides' rows are done
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-      const int q = min(j * W + wv, NB - 1);
-      x[j] = ur[lane_i32(qm.z, q) + (int64_t)lane_rank(qmask(q))];
-    }
+    for (int i = 0; i < NR; ++i) {
+      if (!on[i]) continue;
+      // Every lane loads (an absent node's lane the block's first value, which
+      // it drops): under a condition each load would be a basic block of its
+      // own and wait for the one before it.
+      // Cells of absent nodes hold that value: no tile row's stencil has one.
+      const TS* ur = u + (r + i) * ld;
+      TS x[NQ];
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-      const int q = min(j * W + wv, NB - 1);
-      const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
-      const int off = (DIM == 3 ? (qz * BX * EX + qy * BX) * EP : qy * BX * EP) + qx * BX;
-      bool in;
-      if constexpr (W == 1) in = IN.m[q] == ~0ull || lane_in(IN.m[q]);
-      else in = qx * BX + G::lx(lane) < EX && qy * BX + G::ly(lane) < EX && (DIM == 2 || qz * BX + G::lz(lane) < SP::EZ);
-      s_u[in ? cell0 + off : CS] = (double)x[j];
+      for (int j = 0; j < NQ; ++j) {
+        const int q = min(j * W + wv, NB - 1);
+        x[j] = ur[lane_i32(qm.z, q) + (int64_t)lane_rank(qmask(q))];
+      }
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) {
+        const int q = min(j * W + wv, NB - 1);
+        const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
+        const int off = (DIM == 3 ? (qz * BX * EX + qy * BX) * EP : qy * BX * EP) + qx * BX;
+        bool in;
+        if constexpr (W == 1) in = IN.m[q] == ~0ull || lane_in(IN.m[q]);
+        else
+          in = qx * BX + G::lx(lane) < EX && qy * BX + G::ly(lane) < EX &&
+               (DIM == 2 || qz * BX + G::lz(lane) < SP::EZ);
+        s_u[i][in ? cell0 + off : CS] = (double)x[j];
+      }
     }
     __syncthreads();
     for (int k = 64 * wv + lane; k - lane < rg.y; k += 64 * W) {
       const int2 dc = dof;
       const int bc = ((DIM == 3 ? (code >> 8) * EX : 0) + ((code >> 4) & 15)) * EP + (code & 15);
-      double v[2];
-      interp_pair<DIM, NP, EX, EP>(s_u + bc, t, v, [&] { rows(k + 64 * W); });
-      // keeps the sums out of the branches below (the compiler would sink
-      // them there and hold every member in a register for them)
-      asm volatile("" : "+v"(v[0]), "+v"(v[1]));
-      if (k < rg.y) {
-        a[r * ld + dc.x] = v[0];
-        if (dc.y >= 0) a[r * ld + dc.y] = v[1];
-      }
+      interp_pair<DIM, NP, EX, EP, NR>(
+          &s_u[0][bc], CS + 1, on, t, [&] { rows(k + 64 * W); },
+          [&](int i, const double v[2]) {
+            if (k < rg.y) {
+              a[(r + i) * ld + dc.x] = v[0];
+              if (dc.y >= 0) a[(r + i) * ld + dc.y] = v[1];
+            }
+          });
     }
   }
 }
@@ -1146,7 +1184,9 @@ static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hi
   const int64_t g = (int64_t)er.groups / waves + sv.n;
   if (!g) return;
   auto multi = [&](auto pad, auto np) {
-    auto kern = waves == 2 ? k_gather<T, DIM, pad(), np(), 2> : k_gather<T, DIM, pad(), np(), 1>;
+    auto kern = per > 1      ? k_gather<T, DIM, pad(), np(), 2, 2>
+                : waves == 2 ? k_gather<T, DIM, pad(), np(), 2, 1>
+                             : k_gather<T, DIM, pad(), np(), 1, 1>;
     hipLaunchKernelGGL(kern, dim3((unsigned)g, (nrhs + per - 1) / per), dim3(64 * waves), 0, st, er, sv, b->st_meta,
                        b->st_rng, u, a, b->n, nrhs, per, tn.xcd, skip);
   };
