@@ -39,19 +39,19 @@ BYTES_PER_ROW_F64 = 40.0   # per row of the apply: cp_S 24 + u 8 + v 8 (FP64)
 BYTES_PER_ROW_F32 = 24.0   # fraction 12 + base 4 + u 4 + v 4 (FP32 vectors)
 GOLDEN = os.path.join(ROOT, "tests", "golden")
 
-# HBM bytes per launch of the FP64 tile gather on this workload, from two
-# rocprofv3 --pmc runs (FETCH_SIZE, then WRITE_SIZE; summaries and commands in
+# HBM bytes per launch of the FP64 gather of the rows without swaps (a launch
+# of its own, as the phases are timed) on this workload, from two rocprofv3
+# --pmc runs (FETCH_SIZE, then WRITE_SIZE; summaries and commands in
 # profiles/gather_torus512_pmc.md), each scaled by the same counter's reading
 # for a plain device copy of known size.  They hold only for the kernel
 # source they were taken on: `traffic` is null when its hash differs.
-GATHER_PMC = {"sources_sha1": "a2076ed167a9048b0227a02209f59ad9e8eeff7e",
-              "fetch_bytes": 1.56062e+09, "write_bytes": 2.96609e+08}
-# The same runs for the whole FP64 apply (tile gather, explicit E rows,
-# Laplacian pass, explicit L rows; profiles/*_torus512_pmc.md), valid while
-# the hash of apply.hip, lagrange.hpp and builder.hip is the one below.
-APPLY_PMC = {"sources_sha1": "7d585bba18b378b84b2c81d24b10de2c2fb1a1e0",
-             "bytes": {"tile gather": 1.85723e+09, "explicit E rows": 2.07567e+08,
-                       "block Laplacian": 1.05252e+09, "explicit L rows": 1.61315e+07}}
+GATHER_PMC = {"sources_sha1": "d638a5d65100420719b04c2ee4d1ede7b3cd991e",
+              "fetch_bytes": 1.49060e+09, "write_bytes": 4.79919e+08}
+# The same runs for the whole FP64 apply (gather with explicit E rows,
+# Laplacian pass with explicit L rows; profiles/*_torus512_pmc.md), valid
+# while the hash of apply.hip, lagrange.hpp and builder.hip is the one below.
+APPLY_PMC = {"sources_sha1": "5eb2c2726134ee761a63c3c66461701551d3c49c",
+             "bytes": {"gather": 2.05169e+09, "Laplacian": 9.64021e+08}}
 
 
 def _code(text):
@@ -774,7 +774,8 @@ def main():
                                      "explicit L rows"]},
         "time_to_1e-8": solves,
         "configs": configs,
-        "autotune": {"variants": "k = 8 * lap + 2 * mode + pad (mode 0 block order, 1 XCD-aware, 2 persistent XCD-aware gather, 3 persistent pipelined gather; lap 0..3 the forms of the Laplacian pass, 3 = two blocks per wave with scalar metadata)", "f64_ms": tune64[0], "f64_best": tune64[1],
+        "autotune": {"variants": "k = 8 * lap + 2 * mode + pad (mode 0 block order, 1 to 3 XCD-aware; "
+                     "lap selects nothing: four distinct variants, each timed once)", "f64_ms": tune64[0], "f64_best": tune64[1],
                      "f32_ms": tune32[0], "f32_best": tune32[1]},
         "build_band_s": build_s,
         "adjoint": adjoint,

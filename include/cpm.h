@@ -231,12 +231,14 @@ cpm_status cpm_apply_noalloc(const cpm_band* band, double m, double n, int dtype
                              int nrhs, const void* u, void* v, void* hip_stream);
 
 /* z = A^T w = m w + n diag(L) w + n E^T ((L - diag L)^T w): the transpose of
- * cpm_apply (derived from Sec. 5.4).  Every sum has a fixed order (per-supertile
- * sums in LDS, then added node by node in one order; explicit rows through
- * pull lists), so the
- * result is the same bit for bit on every call.  Arguments and precision as
- * for cpm_apply (FP64 intermediates (L - diag L)^T w and E^T of it for both
- * dtypes); CPM_E_INVALID also for a band without a transpose schedule. */
+ * cpm_apply (derived from Sec. 5.4).  Every sum has a fixed order
+ * (per-supertile sums in LDS, then added node by node in one order; explicit
+ * rows through pull lists), so the result is the same bit for bit on every
+ * call.  Arguments and precision as for cpm_apply (FP64 intermediates
+ * (L - diag L)^T w and E^T of it for both dtypes); CPM_E_INVALID also for a
+ * band without a transpose schedule.  Scratch per right-hand side: 8 n bytes, and
+ * 6.8 KB a supertile (4.2 KB in 2-D) for as many of them
+ * at a time as fit into 256 MiB, at least one. */
 cpm_status cpm_apply_transpose(const cpm_band* band, double m, double n,
                                int dtype, int nrhs, const void* w, void* z,
                                void* hip_stream);

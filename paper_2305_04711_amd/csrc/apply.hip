@@ -257,9 +257,10 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s0, int c
 // interpolates two rows of one stencil base reads the members once for both,
 // and the pooled slots of 2 x 2 tiles fill 77% of the lanes: LDS busy 52%.
 // The staged blocks' loads, each under a branch of its own, also waited for
-// one another; all 18 are now in flight at once.  The kernel then moves
-// 2.2 GB at 5.0 TB/s (explicit rows included, 0.48 ms against 0.55 ms), the
-// rate of a large copy.  Four such tiles by four wavefronts with a barrier
+// one another; all 18 are now in flight at once.  The kernel then moves 2.0
+// GB at 4.2 TB/s (explicit rows included, 0.48 ms against 0.55 ms), with the
+// vector unit busy 60% and the LDS 56% of the time.  Four such tiles by four
+// wavefronts with a barrier
 // (27 blocks) took 0.63 ms and a persistent pipeline over them 0.55 ms:
 // wavefronts that wait for one another hold their slots idle.
 // Registers, not LDS, set the occupancy (4 or 5 wavefronts per SIMD, which
@@ -1313,12 +1314,14 @@ void apply_impl(const cpm_band* b, double m, double n, int nrhs, const T* u, T* 
 }
 
 // Right-hand sides of one transposed gather: its buffer takes CELLS entries a
-// supertile each, so several share it only while it stays small.
+// supertile each, so several share it only while it stays small (and their
+// number is a grid dimension).
 constexpr size_t kTransposeBufBytes = size_t(256) << 20;
+constexpr size_t kMaxTransposeRhs = 32768;
 static int transpose_rhs(const cpm_band* b, int nrhs) {
   const size_t one = sizeof(double) * (size_t)b->nst *
                      (b->dim == 3 ? Super<3>::CELLS : Super<2>::CELLS);
-  const size_t k = one ? kTransposeBufBytes / one : (size_t)nrhs;
+  const size_t k = one ? std::min(kTransposeBufBytes / one, kMaxTransposeRhs) : kMaxTransposeRhs;
   return (int)std::max<size_t>(1, std::min<size_t>(k, (size_t)nrhs));
 }
 
