@@ -245,10 +245,10 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s0, int c
 }
 
 // Pass 1 in one launch, W wavefronts to a workgroup: the first sv.n take a
-// supertile each, the last ones explicit rows.  Those are short and fill the chip
-// while the last supertiles end: first in the grid they cost the whole apply
-// 22.6, 149 and 756 us against 18.2, 143 and 745 us (sphere at h = 1/64, FP64,
-// and 1/256, FP32; torus at 1/512, FP64).
+// supertile each, the last ones explicit rows.  Those are short and fill the
+// chip while the last supertiles end: first in the grid they cost the whole
+// apply 22.6, 149 and 756 us against 18.2, 143 and 745 us (sphere at h = 1/64,
+// FP64, and 1/256, FP32; torus at 1/512, FP64).
 //
 // What bounds it: with one tile per wavefront and one row per lane every row
 // read its 4^d members from LDS by itself, at 128 B a clock and CU, with 71%
@@ -260,11 +260,11 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s0, int c
 // one another; all 18 are now in flight at once.  The kernel then moves 2.0
 // GB at 4.2 TB/s (explicit rows included, 0.48 ms against 0.55 ms), with the
 // vector unit busy 60% and the LDS 56% of the time.  Four such tiles by four
-// wavefronts with a barrier
-// (27 blocks) took 0.63 ms and a persistent pipeline over them 0.55 ms:
-// wavefronts that wait for one another hold their slots idle.
-// Registers, not LDS, set the occupancy (4 or 5 wavefronts per SIMD, which
-// time the same); forcing a sixth spills and loses.
+// wavefronts with a barrier (27 blocks) took 0.63 ms and a persistent pipeline
+// over them 0.55 ms: wavefronts that wait for one another hold their slots
+// idle.  Registers, not LDS, set the occupancy (4 or 5 wavefronts per SIMD);
+// forcing a sixth spills and loses.
+
 // Two wavefronts share a supertile where supertiles are few or take several
 // right-hand sides in turn: half the chain of each, next to a barrier.
 // Transpose of one column, one wavefront, two: 28.6, 21.8 us at 600
@@ -1188,8 +1188,8 @@ static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hi
     auto kern = per > 1      ? k_gather<T, DIM, pad(), np(), 2, 2>
                 : waves == 2 ? k_gather<T, DIM, pad(), np(), 2, 1>
                              : k_gather<T, DIM, pad(), np(), 1, 1>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)g, (nrhs + per - 1) / per), dim3(64 * waves), 0, st, er, sv, b->st_meta,
-                       b->st_rng, u, a, b->n, nrhs, per, tn.xcd, skip);
+    hipLaunchKernelGGL(kern, dim3((unsigned)g, (nrhs + per - 1) / per), dim3(64 * waves), 0, st,
+                       er, sv, b->st_meta, b->st_rng, u, a, b->n, nrhs, per, tn.xcd, skip);
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;

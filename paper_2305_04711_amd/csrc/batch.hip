@@ -7,8 +7,9 @@
 // stored in each block's metadata.  The Krylov solver is BiCGSTAB with one
 // set of scalars and one convergence flag per system (instance, right-hand
 // side): every reduction is segmented over fixed chunks of one system, whose
-// partials the next kernel adds up in a fixed order.  Mixed precision works as for one band: FP32 BiCGSTAB for the
-// correction inside FP64 iterative refinement, per system.
+// partials the next kernel adds up in a fixed order.  Mixed precision works as
+// for one band: FP32 BiCGSTAB for the correction inside FP64 iterative
+// refinement, per system.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
