@@ -13,6 +13,8 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdio>
+#include <cstdlib>
 #include <memory>
 
 #include "cpm_internal.hpp"
@@ -126,16 +128,17 @@ __device__ __forceinline__ void seg_add(const double* __restrict__ part, int nch
   const int s = g.csys[blockIdx.x];                   \
   const int64_t lo = g.clo[blockIdx.x], hi = g.chi[blockIdx.x]
 
-// r = b - v, rh = r, and the partials of (r, r), (b, b) of active systems
+// r = b - ax (b where ax is null), rh = r, and the partials of (r, r), (b, b)
+// of active systems
 template <class T>
 __global__ __launch_bounds__(256) void k_binit(int nchunks, Seg g, const T* __restrict__ b,
-                                               const T* __restrict__ v, int has_v, T* r, T* rh,
+                                               const T* __restrict__ ax, T* r, T* rh,
                                                double* part, const BScal* S) {
   SEG_PROLOGUE;
   if (!S[s].active) return;
   double acc[2] = {0.0, 0.0};
   for (int64_t i = lo + threadIdx.x; i < hi; i += kBT) {
-    const T ri = has_v ? b[i] - v[i] : b[i];
+    const T ri = ax ? b[i] - ax[i] : b[i];
     r[i] = ri;
     rh[i] = ri;
     acc[0] += (double)ri * (double)ri;
@@ -561,6 +564,16 @@ constexpr int kAutotuneSlot = 90;
 
 Seg seg_of(const cpm_batch* B) { return Seg{B->csys, B->clo, B->chi, B->sfirst, B->snch}; }
 
+// Test hook for the restart of one system: CPM_TEST_BATCH_BREAKDOWN=s:k makes
+// an FP64 batched solve take system s as broken down once, at its first check
+// after k iterations.  Read per solve; {-1, 0} when unset.
+std::pair<int, int> test_breakdown() {
+  const char* e = std::getenv("CPM_TEST_BATCH_BREAKDOWN");
+  int s = -1, k = 0;
+  if (!e || std::sscanf(e, "%d:%d", &s, &k) != 2) return {-1, 0};
+  return {s, k};
+}
+
 struct PinnedB {
   BScal* h = nullptr;
   explicit PinnedB(int n) { CPM_HIP(hipHostMalloc((void**)&h, sizeof(BScal) * n, hipHostMallocDefault)); }
@@ -629,14 +642,14 @@ struct BBicg {
       if constexpr (std::is_same<T, TX>::value) apply(x, v);
       else CPM_FAIL(CPM_E_INVALID, "internal: warm start of a mixed-type recurrence");
     }
-    start(rhs, x_zero ? 0 : 1, tol);
+    start(rhs, x_zero ? nullptr : v, tol);
   }
-  // r = rhs - v (or rhs) and the scalars of the active systems; the partials
-  // of the others stay as they are.  counts (optional): scalars that hold the
-  // iterations so far.
-  void start(const T* rhs, int has_v, double tol, const BScal* counts = nullptr) {
+  // r = rhs - ax (rhs where ax is null) and the scalars of the active systems;
+  // the partials of the others stay as they are.  counts (optional): scalars
+  // that hold the iterations so far.
+  void start(const T* rhs, const T* ax, double tol, const BScal* counts = nullptr) {
     hipLaunchKernelGGL(k_binit<T>, dim3(B->nchunks), dim3(kBT), 0, st, B->nchunks, seg_of(B), rhs,
-                       v, has_v, r, rh, part, S);
+                       ax, r, rh, part, S);
     hipLaunchKernelGGL(k_binit_fin, dim3(B->nsys), dim3(kBT), 0, st, B->nchunks, seg_of(B), part,
                        S, tol, counts);
     CPM_LAUNCH_CHECK();
@@ -701,6 +714,7 @@ struct BBicg {
     init(rhs, x, x_zero, tol);
     const BScal* h = read();
     int it = 0;
+    auto force = test_breakdown();
     for (int restarts = 0;;) {
       bool all = true;
       std::vector<int> rs(B->nsys, 0);
@@ -708,6 +722,10 @@ struct BBicg {
       for (int q = 0; q < B->nsys; ++q) {
         if (!h[q].done) all = false;
         rs[q] = hact[q] && h[q].done && h[q].breakdown && !(h[q].rr <= h[q].tol2);
+        if (q == force.first && hact[q] && !h[q].done && h[q].it >= force.second) {
+          rs[q] = 1;
+          force.first = -1;
+        }
         any_rs |= rs[q] != 0;
         it = std::max(it, h[q].it);
       }
@@ -721,8 +739,10 @@ struct BBicg {
         set_active(rs);
         hipLaunchKernelGGL(k_bset_active, dim3((B->nsys + 127) / 128), dim3(128), 0, st, S,
                            B->nsys, act);
-        apply(x, v);    // covers every system, whatever its state
-        start(rhs, 1, tol, S + 2 * B->nsys);
+        // A x of every system, into t: an iteration writes t before it reads
+        // it, but begins with the v of the one before
+        apply(x, t);
+        start(rhs, t, tol, S + 2 * B->nsys);
         set_active(keep);
         hipLaunchKernelGGL(k_bset_active, dim3((B->nsys + 127) / 128), dim3(128), 0, st, S,
                            B->nsys, act);
