@@ -989,12 +989,13 @@ __global__ void k_pull_pairs_l(int nrows, int nf, int64_t n_s, const int* row_id
   val[g] = 2 * i + sgn;
 }
 
-// E pull entries in sorted order: the source's weight and its row's DOF, which replaces the source index in place
+// E pull entries in sorted order: the source's weight and its row's DOF, which
+// replaces the source index in place
 template <int DIM>
 __global__ void k_pull_denorm_e(int total, int* src, int p, const int* erow_id, const double* ew1,
                                 double* w64) {
   constexpr int NM = DIM == 3 ? 64 : 16;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int g = src[e];
   w64[e] = erow_weight<DIM>(ew1 + (int64_t)(g / NM) * 4 * DIM, erow_member<DIM>(p, g % NM));

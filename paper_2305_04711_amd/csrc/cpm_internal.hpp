@@ -337,11 +337,19 @@ size_t apply_scratch_bytes(const cpm_band* b, int nrhs);
 void add_dirichlet_term(const cpm_band* b, double n, const double* g, int nrhs, double* out,
                         hipStream_t st);
 
-inline int grid_for(int64_t n, int threads, int cap = 1 << 20) {
-  int64_t g = (n + threads - 1) / threads;
-  if (g < 1) g = 1;
-  if (g > cap) g = cap;
+// Workgroups that hold n items, one to a thread (at least one workgroup).  A
+// launch holds fewer than 2^32 threads.
+inline int grid_for(int64_t n, int threads) {
+  const int64_t g = n > 0 ? (n + threads - 1) / threads : 1;
+  if (g * threads >= (1ll << 32))
+    CPM_FAIL(CPM_E_INVALID, "%lld items are too many for a launch", (long long)n);
   return static_cast<int>(g);
+}
+// The same, at most cap of them, for kernels that go through their items in
+// strides of the grid.
+inline int grid_for(int64_t n, int threads, int cap) {
+  const int64_t g = n > 0 ? (n + threads - 1) / threads : 1;
+  return static_cast<int>(g < cap ? g : cap);
 }
 
 }  // namespace cpm
