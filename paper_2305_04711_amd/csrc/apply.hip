@@ -397,6 +397,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((
 // Workgroup sums of d0 and d1 (256 threads, every one must call it), written
 // to part[idx] and part[np + idx]: the partials of a fused dot product, one
 // per workgroup, finished in a fixed order by the solver.
+static_assert(kLapThreads == 256, "four wavefronts");
 __device__ __forceinline__ void group_dot2(double d0, double d1, double* part, int np, int idx) {
   __shared__ double sh[4][2];
   d0 = lanes_sum<64>(d0);
@@ -529,14 +530,10 @@ struct DotOut {
   int np;
 };
 
-// two blocks per wavefront: one 0.308, two 0.270, four 0.296 ms at 34.1M rows
-constexpr int kLapBlocksPerWave = 2;
-constexpr int kLapBlocksPerGroup = 4 * kLapBlocksPerWave;
-
 // The first lr.groups workgroups take explicit rows (ALL: the BC entries), the
 // others blocks.
 template <class TU, class TA, class TV, int DIM, bool ALL, bool DOT = false>
-__global__ __launch_bounds__(256) void k_lap(
+__global__ __launch_bounds__(kLapThreads) void k_lap(
     LRows lr, LPull lp, const QMeta* __restrict__ face, int nb, const TU* __restrict__ u,
     const TA* __restrict__ a, TV* __restrict__ v, int64_t ld, int nrhs, int per, double cd, double co,
     const double* __restrict__ gsum, double gscale, int xcd, const double* __restrict__ coef,
@@ -556,7 +553,7 @@ __global__ __launch_bounds__(256) void k_lap(
     return;
   }
   if (!ALL && (int)blockIdx.x < lr.groups) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * kLapThreads + threadIdx.x;
     const int id = i < lr.n ? lr.id[i] : -1;
     const int inst = coef && id >= 0 ? lr.inst[i] : 0;
     if (coef && id >= 0) {
@@ -1209,7 +1206,9 @@ static void launch_gather(const cpm_band* b, int nrhs, const T* u, double* a, hi
 static int lap_groups(const cpm_band* b) {
   return (b->nb + kLapBlocksPerGroup - 1) / kLapBlocksPerGroup;
 }
-static int lap_row_groups(const cpm_band* b) { return (b->n_lrows + 255) / 256; }
+static int lap_row_groups(const cpm_band* b) {
+  return (b->n_lrows + kLapThreads - 1) / kLapThreads;
+}
 static int bc_groups(const cpm_band* b) { return (int)((b->n_c + 255) / 256); }
 
 // Number of partials a fused dot product of an apply writes (per value): one
@@ -1232,7 +1231,7 @@ static void launch_lap(const cpm_band* b, const Tune& tn, hipStream_t st, const 
   // in a solver too: apart they read the blocks' masks each (203 against 196 ms)
   const int per = rhs_per_group(b, nrhs, Skip{});
   hipLaunchKernelGGL((k_lap<TU, TA, TV, DIM, ALL, DOT>), dim3((unsigned)g, (nrhs + per - 1) / per),
-                     dim3(256), 0, st, lr, lp, b->blk_face, b->nb, u, a, v, ld, nrhs, per, cd, co,
+                     dim3(kLapThreads), 0, st, lr, lp, b->blk_face, b->nb, u, a, v, ld, nrhs, per, cd, co,
                      gsum, gscale, tn.xcd, coef, skip, dot);
   CPM_LAUNCH_CHECK();
 }

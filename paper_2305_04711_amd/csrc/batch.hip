@@ -418,7 +418,7 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   c->composite = true;
   // blocks and explicit FD rows of an instance are padded to whole workgroups
   // of the Laplacian pass, so that a workgroup's dot partial has one owner
-  constexpr int kBlkPad = 8, kRowPad = 256;
+  constexpr int kBlkPad = kLapBlocksPerGroup, kRowPad = kLapThreads;
   auto up = [](int64_t n, int to) { return (n + to - 1) / to * to; };
   int64_t nb = 0, nt = 0, ns = 0, ne = 0, nl = 0;
   B->D.assign(ni + 1, 0);

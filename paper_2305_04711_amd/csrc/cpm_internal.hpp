@@ -314,6 +314,14 @@ struct Skip {
   int stride = 1, elem = 1;
 };
 
+// The Laplacian pass takes kLapBlocksPerWave blocks to a wavefront (one 0.308,
+// two 0.270, four 0.296 ms at 34.1M rows), and an explicit FD row to a thread.
+// A batch pads an instance's blocks and rows to whole workgroups, so that each
+// workgroup has one instance.
+constexpr int kLapThreads = 256;
+constexpr int kLapBlocksPerWave = 2;
+constexpr int kLapBlocksPerGroup = kLapThreads / 64 * kLapBlocksPerWave;
+
 // apply entry points used by the solvers (optional gauge).  With dy set, the
 // kernel that writes v also writes the partials of (dy, v) and (v, v) of
 // right-hand side r to dpart + 2 r np and np entries further, np =
