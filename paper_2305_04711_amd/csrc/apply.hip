@@ -21,11 +21,6 @@ namespace cpm {
 
 // Wave-uniform broadcast of lane k (k must be the same in every lane).
 __device__ __forceinline__ int lane_i32(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
-__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int k) {
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, k);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), k);
-  return ((unsigned long long)hi << 32) | lo;
-}
 
 // With a wave-uniform mask m (in scalar registers): base + the number of
 // bits of m below the lane (masked bit counts, two vector instructions), and
@@ -424,9 +419,11 @@ __device__ __forceinline__ double lap_out(double cd, double u, double co, double
 // wavefront.  A form with per-lane mask arithmetic is bound by vector issue
 // (about 250 vector instructions per block, almost all of them integer work
 // on 64-bit masks), so the index arithmetic is kept off the vector unit:
-//   * the block's metadata (its own and its face neighbours' masks and first
-//     DOFs, the explicit-row mask) is read with scalar loads: every mask is
-//     wave-uniform and stays in scalar registers;
+//   * the blocks' metadata (their own and their face neighbours' masks and
+//     first DOFs, the explicit-row masks) comes in one vector load, an entry to
+//     a lane, and is broadcast from there: every mask is wave-uniform and stays
+//     in scalar registers (a chain of scalar loads: 315 us for 290 at 34.1M
+//     rows);
 //   * lane sets (present slots, output rows, the lanes on a face whose
 //     neighbour across it is present) are built with scalar mask arithmetic
 //     and applied as execution masks (inverse ballot);
@@ -1534,7 +1531,7 @@ extern "C" cpm_status cpm_autotune(cpm_band* b, int dtype, int nrhs, const void*
     try {
       for (int k = 0; k < kTuneVariants; ++k) {
         tn = tune_variant(k);
-        if (((k >> 1) & 3) >= 2 && b->composite) {   // single bands only
+        if (((k >> 1) & 3) >= 2 && b->composite) {   // a batch reports mode 1 only
           t[k] = HUGE_VAL;
           continue;
         }

@@ -378,7 +378,6 @@ struct cpm_batch {
   int64_t* chi = nullptr;
   int* sfirst = nullptr;
   int* snch = nullptr;
-  std::vector<int> h_csys;
   // per instance, the workgroups of the Laplacian pass that hold its blocks
   // and its explicit FD rows ([ninst + 1] each): the partials of a dot product
   // fused into the composite apply that belong to the instance
@@ -556,7 +555,6 @@ void build_composite(cpm_batch* B, hipStream_t st) {
   CPM_HIP(hipMemcpy(B->chi, chi.data(), sizeof(int64_t) * chi.size(), hipMemcpyHostToDevice));
   CPM_HIP(hipMemcpy(B->sfirst, sfirst.data(), sizeof(int) * B->nsys, hipMemcpyHostToDevice));
   CPM_HIP(hipMemcpy(B->snch, snch.data(), sizeof(int) * B->nsys, hipMemcpyHostToDevice));
-  B->h_csys = csys;
 }
 
 // scratch slots of the composite band holding cpm_batch_autotune's vectors
