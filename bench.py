@@ -10,7 +10,7 @@ Timed step: one FP64 application of A = m I + n [diag L + (L - diag L) E]
 (m = 0, n = -1: Poisson) to a vector resident in HBM; value = DOFs / step
 time in Gnodes/s.  Also reported on the same line: the FP32 apply rate, the
 per-phase time of the apply from HIP events on its stream, the roofline of
-the dominant kernel (the tile gather) and of the whole apply, the transposed
+the dominant kernel (the gather) and of the whole apply, the transposed
 apply, the time to a relative residual of 1e-8 for the mixed-precision and
 the plain FP64 solve (median of repeated runs), the solves of the other
 target configurations with their error against the oracle's solution
@@ -45,13 +45,13 @@ GOLDEN = os.path.join(ROOT, "tests", "golden")
 # profiles/gather_torus512_pmc.md), each scaled by the same counter's reading
 # for a plain device copy of known size.  They hold only for the kernel
 # source they were taken on: `traffic` is null when its hash differs.
-GATHER_PMC = {"sources_sha1": "d638a5d65100420719b04c2ee4d1ede7b3cd991e",
-              "fetch_bytes": 1.49060e+09, "write_bytes": 4.79919e+08}
+GATHER_PMC = {"sources_sha1": "b2632d0fd267fbedf817f0d4828aff110239fdc9",
+              "fetch_bytes": 1.48856e+09, "write_bytes": 4.86008e+08}
 # The same runs for the whole FP64 apply (gather with explicit E rows,
 # Laplacian pass with explicit L rows; profiles/*_torus512_pmc.md), valid
 # while the hash of apply.hip, lagrange.hpp and builder.hip is the one below.
-APPLY_PMC = {"sources_sha1": "5eb2c2726134ee761a63c3c66461701551d3c49c",
-             "bytes": {"gather": 2.05169e+09, "Laplacian": 9.64021e+08}}
+APPLY_PMC = {"sources_sha1": "04a179e346034d6ae07223b028c17e7dd50b9947",
+             "bytes": {"gather": 2.06012e+09, "Laplacian": 9.64027e+08}}
 
 
 def _code(text):
@@ -583,7 +583,7 @@ def main():
     dt32 = timed(u32, v32, 1)
     ph64, _ = cpm.apply_profile(band, u64, m, n, reps=max(10, args.steps))
     ph32, _ = cpm.apply_profile(band, u32, m, n, reps=max(10, args.steps))
-    # rows processed by the tile gather = PDE rows without swapped members
+    # rows of the gather proper = PDE rows without swapped members
     tile_rows = band.n_s - (info["n_erows"] - band.n_c)
     ach64 = BYTES_PER_ROW_F64 * tile_rows / (ph64[0] * 1e-3) / 1e9
     ach32 = BYTES_PER_ROW_F32 * tile_rows / (ph32[0] * 1e-3) / 1e9
@@ -744,7 +744,7 @@ def main():
         "config": {"workload": "torus R=1 rho=0.4, h=1/%d, two second-order Dirichlet meridian "
                                "IBCs (toroidal angles 0, pi); Poisson m=0 n=-1" % N,
                    "n_s": info["n_s"], "n_c": info["n_c"], "dofs": dofs},
-        "roofline": {"bound": "hbm", "kernel": "k_gather<double,3,1> (tile gather a = E u)",
+        "roofline": {"bound": "hbm", "kernel": "k_gather<double,3,1> (a = E u, rows without swaps)",
                      "achieved": ach64, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": ach64 / HBM_PEAK_GBS, "traffic": traffic,
                      "bytes_per_row": BYTES_PER_ROW_F64, "rows_per_launch": tile_rows,
@@ -770,12 +770,14 @@ def main():
                       "gather_gbs": ach32, "gather_frac": ach32 / HBM_PEAK_GBS},
         "transpose_apply_ms": {"f64": dtT64 * 1e3, "f32": dtT32 * 1e3},
         "apply_phase_ms": {"f64": ph64, "f32": ph32,
-                           "order": ["tile gather", "explicit E rows", "block Laplacian",
-                                     "explicit L rows"]},
+                           "order": ["gather of rows without swaps", "explicit E rows",
+                                     "block Laplacian", "explicit L rows"]},
         "time_to_1e-8": solves,
         "configs": configs,
-        "autotune": {"variants": "k = 8 * lap + 2 * mode + pad (mode 0 block order, 1 to 3 XCD-aware; "
-                     "lap selects nothing: four distinct variants, each timed once)", "f64_ms": tune64[0], "f64_best": tune64[1],
+        "autotune": {"variants": "k = 8 * lap + 2 * mode + pad (mode 0 block order, 1 to 3 "
+                                 "XCD-aware; lap selects nothing: four distinct variants, each "
+                                 "timed once)",
+                     "f64_ms": tune64[0], "f64_best": tune64[1],
                      "f32_ms": tune32[0], "f32_best": tune32[1]},
         "build_band_s": build_s,
         "adjoint": adjoint,

@@ -323,7 +323,7 @@ cpm_status cpm_heat_cn(const cpm_band* band, double dt, int nsteps,
 
 /* Measurement: run cpm_apply `reps` times on hip_stream with HIP events
  * around each of its four phases and return the mean milliseconds per call in
- * ms[4]: [0] tile gather (a = E u for rows without swaps), [1] explicit
+ * ms[4]: [0] gather (a = E u for rows without swaps), [1] explicit
  * interpolation rows, [2] block Laplacian pass, [3] explicit FD rows.
  * Synchronises the stream.  Arguments as for cpm_apply. */
 cpm_status cpm_apply_profile(const cpm_band* band, double m, double n, int dtype,

@@ -261,8 +261,8 @@ apply_cpm = apply
 
 def apply_profile(band, u, m, n, reps=20):
     """Mean milliseconds per phase of cpm_apply over `reps` calls, timed with
-    HIP events on the launch stream: (tile gather, explicit E rows, block
-    Laplacian, explicit L rows)."""
+    HIP events on the launch stream: (gather of the rows without swaps,
+    explicit E rows, block Laplacian, explicit L rows)."""
     nrhs = _check_vec(band, u, band.n)
     v = torch.empty_like(u)
     ms = (C.c_double * 4)()

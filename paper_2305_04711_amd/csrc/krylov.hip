@@ -62,9 +62,12 @@ constexpr int kRedThreads = 256;
 constexpr int kMaxParts = 1024;
 // Partials that every workgroup of a consumer adds up by itself, kPartLoads
 // loads of a thread at once (one at a time: 60.3 us an iteration at 0.44M DOFs
-// and 1400 partials, 58.8 now); more are added by k_parts to kFoldParts first.
-// At 2900 partials an iteration takes 113.8 us without k_parts and 118.2 with
-// it; from 4096 on each workgroup would read more than 64 KB.
+// and 1383 partials, 58.4 now); more are added by k_parts to kFoldParts first.
+// An iteration without k_parts and with it, FP64 spheres of 0.44M to 6.9M DOFs:
+// 58.4, 63.4 us at 1383 partials, 91.0, 93.5 at 3030, 109.4, 110.8 at 4104;
+// 145.6, 146.1 at 6026; 214.7, 210.1 at 8249, 531, 504 at 20921.  The line lies
+// a little before the two cross, where they differ by 1%, and bounds what a
+// workgroup reads at 64 KB.
 constexpr int kDirectParts = 4096;
 constexpr int kPartLoads = 8;
 constexpr int kFoldParts = 256;
