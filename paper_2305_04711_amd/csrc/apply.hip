@@ -252,8 +252,8 @@ __device__ __forceinline__ void interp_pair(const double* __restrict__ s0, int c
 // interpolates two rows of one stencil base reads the members once for both,
 // and the pooled slots of 2 x 2 tiles fill 77% of the lanes: LDS busy 52%.
 // The staged blocks' loads, each under a branch of its own, also waited for
-// one another; all 18 are now in flight at once.  The kernel then moves 2.0
-// GB at 4.2 TB/s (explicit rows included, 0.48 ms against 0.55 ms), with the
+// one another; all 18 are now in flight at once.  The kernel moves 2.06
+// GB at 4.4 TB/s (explicit rows included, 0.47 ms against 0.55 ms), with the
 // vector unit busy 60% and the LDS 56% of the time.  Four such tiles by four
 // wavefronts with a barrier (27 blocks) took 0.63 ms and a persistent pipeline
 // over them 0.55 ms: wavefronts that wait for one another hold their slots
